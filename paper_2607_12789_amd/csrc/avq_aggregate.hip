@@ -1,111 +1,66 @@
 // Per-codeword counts and value sums, Eq. (aggregates), with the Alg. 1
 // convention that a parent row covers its whole cell and a child row the keys
-// that moved to it.
+// that moved to it; and the same pass with the child compare of Alg. 1 in it.
 //
-// One workgroup owns one (batch, head) and a range of 32 parent families (a
-// family = parent p and its Ch children); each half wave (32 lanes) owns one
-// family and is the only writer of its rows, so no float atomics are needed
-// (LDS float atomics serialise on gfx950; integer ones do not). The
-// workgroup
-//   1. scans the codes of every key of the head (the next round's codes are
-//      prefetched while the current one is queued) and appends the keys whose
-//      parent is in its range to an LDS queue, in key order (wave ballot +
-//      prefix counts);
-//   2. when the queue is full or the codes are exhausted, buckets the queued
-//      keys by their row (stay row of the parent, or one of its children) with
-//      integer LDS atomics: histogram, prefix sum, scatter;
-//   3. lets each half wave walk its family's keys in bucket order through a
-//      ring of 8 value rows (4 for Ch = 16) in flight, whatever rows they
-//      belong to, each slot refilled as soon as its row is added (lane l
-//      holds columns l*CPL .. l*CPL+CPL-1), summing in fp32 into a running
-//      row sum that is added to the family's register table when the row
-//      ends.
-// At the end the parent row is the stay row plus the children (the whole
-// cell), every row is written once, and counts come from the histograms.
-// Optionally the packed aggregates are also written (avq_packed.hpp): the
-// mean value (sum / count) of every code rounded to the input type, in octets
-// of 8 codes laid out as the attention kernel's MFMA operands, [octet][d][8],
-// with n and ln n per code.
+// A family is a parent and its Ch children (Ch = 0, a flat codebook: 16
+// consecutive parents). One workgroup owns one (batch, head) and a range of F
+// families and is the only writer of their rows, so there are no float
+// atomics and no partial results in HBM. The workgroup
+//   1. counts the head's keys per family (one scan of the codes, integer LDS
+//      atomics) and gives every family whole groups of 32 slots in a key list;
+//   2. scans the codes again and scatters the keys into their family's slots;
+//   3. deals the groups to its waves in equal contiguous runs. For a group
+//      of 32 keys of one family a wave reads the 32 value rows (FUSED: and
+//      the 32 key rows, whose child compare, avq_child.hpp, tells each key's
+//      row), and adds them with matrix products: sums^T += onehot . V, where
+//      row x of the 16 x 32 one-hot operand has a 1 for every key of row x
+//      and row 8 a 1 for every key (the whole cell). Products with 0 and 1
+//      are exact, the sums are fp32, and the same product with a column of
+//      ones gives the counts. So the keys of a family need no order, the rows
+//      of K and V arrive together, and a key costs one MFMA column instead of
+//      an unpack and an add per value;
+//   4. a wave that holds all of a family's groups writes its rows; the parts
+//      of a family that spans waves meet in LDS, added in wave order by the
+//      wave that holds the family's first group.
+// The next group's rows are requested as soon as a group's registers are
+// consumed, so a wave always has 8 (FUSED: 16 at d = 128) row loads in flight.
+//
+// The key list takes the LDS that is left. A range with more keys takes its
+// families in batches that fit, and a single family that does not fit takes
+// its keys in segments of the head, with the sums kept in registers from one
+// to the next.
+//
+// What bounds it: at large sizes HBM (each value and key row is read once),
+// at small ones the chain of phases of one workgroup. Measured (traced, bf16,
+// the fused pass; before: keys bucketed a second time by row, each half wave
+// summing one family's rows in turn with vector adds): B = 2, H = 16,
+// N = 16384, d = 128, M0 = 256, Ch = 8: 75 -> 68 us (4.7 TB/s while the rows
+// stream); B = 4, H = 12, N = 1024, d = 64, M0 = 64, Ch = 8: 29 -> 21 us;
+// B = 8, H = 12, N = 4096, d = 64, M0 = 256, Ch = 8: 73 -> 65 us.
+//
+// Packed aggregates (avq_packed.hpp): the mean value (sum / count) of every
+// code rounded to the input type, in octets of 8 codes laid out as the
+// attention kernel's MFMA operands, [octet][d][8], with n and ln n per code.
+// Rows 0 .. 7 of an accumulator tile are one child octet (Ch = 16: tile 1 the
+// second; flat: rows 0 .. 7 and 8 .. 15 are two parent octets).
 #include "avq_child.hpp"
 #include "avq_common.hpp"
 #include "avq_launch.hpp"
 #include "avq_packed.hpp"
 
+#include <algorithm>
+
 namespace avq {
 
-constexpr int kAggThreads = 1024;
-constexpr int kAggWaves = kAggThreads / kWave;
-constexpr int kFamLanes = 32;                          // lanes per family
-constexpr int kFamilies = kAggThreads / kFamLanes;     // half waves = most families per workgroup
-constexpr int kCodesPerThread = 8;                     // codes scanned per thread per round
-constexpr int kRound = kAggThreads * kCodesPerThread;
-constexpr int kQueueCap = 8192;                        // queued keys per flush
-constexpr int kMaxRows = kFamilies * 17;               // families x (1 + Ch), Ch <= 16
-// value rows in flight per family: as many as the registers beside the
-// family table (1 + CHM rows of D / 32 sums per lane) allow
-template <int CHM, typename T>
-constexpr int kInFlight = CHM > 8 ? 4 : (CHM == 0 && sizeof(T) == 2) ? 16 : 8;
+constexpr int kMaxFamilies = 32;  // families per workgroup, at most
+constexpr int kGroup = 32;        // keys per group
 
-struct AggLds {
-  int qkey[kQueueCap];       // queued keys, key order
-  uint16_t qrow[kQueueCap];  // their family-local row
-  int skey[kQueueCap];       // keys bucketed by row
-  int hist[kMaxRows];        // keys per row in this flush
-  int start[kMaxRows + 1];   // bucket starts
-  int cursor[kMaxRows];      // scatter cursors
-  int total[kMaxRows];       // keys per row over all flushes (the counts)
-  int fstart[kFamilies + 1];      // fused: family buckets of the queue
-  int fcursor[kFamilies];
-  int item_start[kFamilies + 1];  // fused: first group of 16 keys of each family
-  int wave_count[kCodesPerThread][kAggWaves];  // queued keys per (round slot, wave)
-  int wave_off[kCodesPerThread][kAggWaves];    // their queue offsets in this round
-  int round_total;
-};
-static_assert(kCodesPerThread * kAggWaves <= 128, "one wave scans the slot offsets");
-
-// CPL values of type T as one load: 4, 8 or 16 bytes
-template <int BYTES>
-struct Chunk;
-template <>
-struct Chunk<4> {
-  typedef uint32_t type;
-};
-template <>
-struct Chunk<8> {
-  typedef uint2 type;
-};
-template <>
-struct Chunk<16> {
-  typedef uint4 type;
+enum AggMode {
+  kAggCodes,  // codes given, Ch >= 1
+  kAggFlat,   // codes given, Ch = 0
+  kAggFused,  // parent indices given; the child compare writes the codes
 };
 
-// An empty asm statement on each 32-bit word of a loaded value: the value is
-// first used here, as it was loaded, so the compiler can neither move work on
-// it closer to the load nor wait for the load any earlier.
-template <typename R>
-__device__ __forceinline__ void pin_words(R& r) {
-  constexpr int W = sizeof(R) / 4;
-  uint32_t w[W];
-  __builtin_memcpy(w, &r, sizeof(R));
-#pragma unroll
-  for (int j = 0; j < W; ++j) asm volatile("" : "+v"(w[j]));
-  __builtin_memcpy(&r, w, sizeof(R));
-}
-
-// SPLIT half waves share one family (families per workgroup: kFamilies /
-// SPLIT): each sums a contiguous share of the family's keys in every flush,
-// and the shares are added in a fixed order at the end. More than one for
-// heads with many keys per parent, where one half wave's chain of loads
-// would set the time.
-//
-// FUSED (the child compare of Alg. 1 inside the same pass, Ch >= 1): the
-// input is the parent index of every key instead of its code. Each flush
-// first buckets the queued keys by family, then the waves take groups of 16
-// keys of one family and run the child compare on them (the key rows are
-// read here; the candidate rows stay in registers while a wave's groups share
-// the family), write the code of every key and re-queue the keys with their
-// rows; the flush then goes on as above. Keys, and so the K rows, are read
-// once per head; no code round trip between two kernels.
 struct FusedArgs {
   const void* K;   // [B][H][N][d]
   const void* Cp;  // [H][M0][d]
@@ -114,557 +69,668 @@ struct FusedArgs {
   int H;
 };
 
-template <typename T, int D, int CHM, int SPLIT, bool FUSED>
-__global__ __launch_bounds__(kAggThreads) void aggregate_kernel(const T* __restrict__ V,
-                                                                const int32_t* __restrict__ code_idx,
-                                                                float* __restrict__ Vbar,
-                                                                int32_t* __restrict__ counts,
-                                                                unsigned char* __restrict__ packed,
-                                                                int N, int M0, int Ch, int ranges,
-                                                                FusedArgs fa) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  AggLds& L = *reinterpret_cast<AggLds*>(lds_raw);
-  constexpr int CPL = D / kFamLanes;  // columns per lane
-  using Raw = typename Chunk<CPL * sizeof(T)>::type;
-  static_assert(CPL % 2 == 0, "whole pairs of columns per lane");
+// NT: accumulator tiles (and candidate tiles) per family, 1 for Ch <= 8, 2 for
+// Ch = 16.
+template <typename T, int D, int NT, int MODE>
+struct AggCfg {
+  static constexpr bool kB = Elem<T>::kBf16;
+  static constexpr bool kFlat = MODE == kAggFlat;
+  static constexpr bool kFused = MODE == kAggFused;
+  // Waves per workgroup, one workgroup per CU: as many as the registers (16:
+  // 128 per lane, 12: 168, 8: 256) and the LDS (flat at d = 128: 8) allow.
+  static constexpr int kWaves =
+      D == 128 ? (kFlat || NT == 2 ? 8 : kFused ? (kB ? 12 : 8) : (kB ? 16 : 12))
+               : (NT == 2 ? (kFused && !kB ? 8 : 12) : kFused && !kB ? 12 : 16);
+  static constexpr int kThreads = kWaves * kWave;
+  static constexpr int CT = D / 16;            // 16-column tiles
+  static constexpr int ROWS = kFlat ? 16 : NT == 2 ? 17 : 9;  // rows held of a family
+  static constexpr int OCTS = kFlat ? 2 : 1;  // octets written at a time
+  static constexpr int OCT_BYTES = 8 * D * (int)sizeof(T);
+  // LDS: the fixed tables, one partial slot and one staging area per wave,
+  // the parent means of the range, then the key list
+  struct Tables {
+    int hist[kMaxFamilies];        // keys per family
+    int gstart[kMaxFamilies + 1];  // first group of each family of the batch
+    int cursor[kMaxFamilies];      // keys scattered so far
+    float cell[kMaxFamilies];      // cell sizes (n of the parents)
+    uint16_t onehot[kWaves][NT][kGroup];  // row bits of the group's keys
+  };
+  static constexpr int al16(int x) { return (x + 15) / 16 * 16; }
+  static constexpr int OFF_SLOT = al16((int)sizeof(Tables));
+  static constexpr int SLOT_BYTES = al16(ROWS * D * 4 + ROWS * 4);
+  static constexpr int OFF_STAGE = OFF_SLOT + kWaves * SLOT_BYTES;
+  static constexpr int STAGE_BYTES = OCTS * OCT_BYTES;
+  static constexpr int OFF_PMEAN = OFF_STAGE + kWaves * STAGE_BYTES;
+  static constexpr int off_list(int F) {
+    return OFF_PMEAN + (kFlat ? 0 : F * D * (int)sizeof(T));
+  }
+  static_assert(OFF_PMEAN + (kFlat ? 0 : kMaxFamilies * D * (int)sizeof(T)) +
+                        4 * kGroup * kMaxFamilies <= 160 * 1024,
+                "a key list of one group per family fits the LDS");
+};
 
-  const int Mtot = M0 * (1 + Ch);
+// A value row piece of one lane: 16 bytes (bf16 at d = 64: 8), at the
+// lane's columns; column col(t, c) belongs to column tile t.
+template <typename T, int D>
+struct ValRow {
+  static constexpr int W = D * (int)sizeof(T) / 64;  // 32-bit words per lane
+  static constexpr int CPW = W > 4 ? 4 : W;          // ... of one load
+  uint32_t w[W];
+  __device__ __forceinline__ void load(const T* row, int c) {
+    const unsigned char* p = reinterpret_cast<const unsigned char*>(row);
+#pragma unroll
+    for (int i = 0; i < W / CPW; ++i) {
+      if constexpr (CPW == 4) {
+        const uint4 v = *reinterpret_cast<const uint4*>(p + 256 * i + 16 * c);
+        w[4 * i] = v.x;
+        w[4 * i + 1] = v.y;
+        w[4 * i + 2] = v.z;
+        w[4 * i + 3] = v.w;
+      } else {
+        const uint2 v = *reinterpret_cast<const uint2*>(p + 8 * c);
+        w[0] = v.x;
+        w[1] = v.y;
+      }
+    }
+  }
+  // the same from a head's base and a 32-bit byte offset (bf16: a head is
+  // below 4 GiB), so that the base stays in scalar registers
+  __device__ __forceinline__ void load_key(const T* head, uint32_t key, int c) {
+    if constexpr (sizeof(T) == 2) {
+      const uint32_t off = key * (uint32_t)(D * sizeof(T));
+      load(reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(head) + (size_t)(off + (uint32_t)(4 * CPW * c))), 0);
+    } else {
+      load(head + (size_t)key * D, c);
+    }
+  }
+  // first column of the lane's run of consecutive columns, tiles t .. t + RUN - 1
+  static constexpr int RUN = CPW * 4 / (int)sizeof(T);
+  static __device__ __forceinline__ int col(int t, int c) {
+    return (t / RUN) * 16 * RUN + RUN * c + t % RUN;
+  }
+};
+
+template <typename T, int D, int NT, int MODE>
+__global__ __launch_bounds__((AggCfg<T, D, NT, MODE>::kThreads)) void aggregate_kernel(
+    const T* __restrict__ V, const int32_t* __restrict__ code_idx, float* __restrict__ Vbar,
+    int32_t* __restrict__ counts, unsigned char* __restrict__ packed, int N, int M0, int Ch,
+    int F, int ranges, int cap, FusedArgs fa) {
+  using Cfg = AggCfg<T, D, NT, MODE>;
+  constexpr bool kB = Cfg::kB, kFlat = Cfg::kFlat, kFused = Cfg::kFused;
+  constexpr int W = Cfg::kWaves, CT = Cfg::CT, ROWS = Cfg::ROWS;
+  using VR = ValRow<T, D>;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  typename Cfg::Tables& L = *reinterpret_cast<typename Cfg::Tables*>(lds_raw);
+  T* pmean = reinterpret_cast<T*>(lds_raw + Cfg::OFF_PMEAN);  // [F][D]
+  uint32_t* list = reinterpret_cast<uint32_t*>(lds_raw + Cfg::off_list(F));
+
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+  const int g = lane / 16, c = lane % 16;
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int bh = blk / ranges;
-  constexpr int FAM = kFamilies / SPLIT;  // families of this workgroup
-  const int p0 = (blk % ranges) * FAM;
-  const int nfam = min(FAM, M0 - p0);
-  const int rows = nfam * (1 + Ch);
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const int sub = lane % kFamLanes, fam = tid / kFamLanes / SPLIT, part = tid / kFamLanes % SPLIT;
-  const int ch_shift = Ch > 0 ? 31 - __builtin_clz(Ch) : 0;  // Ch = 0: a flat codebook
-
-  for (int r = tid; r < kMaxRows; r += kAggThreads) L.total[r] = 0;
-
+  const PackedLayout PL = packed_layout(M0, Ch, D, (int)sizeof(T));
+  const int n_fam = kFlat ? PL.PO / 2 : M0;  // flat: the padding octets' families too
+  const int p0 = (blk % ranges) * F;
+  const int nfam = min(F, n_fam - p0);
+  const int Mtot = M0 * (1 + Ch);
+  const int ch_shift = kFlat ? 0 : 31 - __builtin_clz(Ch);  // Ch is a power of two
   const int32_t* codes = code_idx + (size_t)bh * N;  // FUSED: parent indices
   const T* vhead = V + (size_t)bh * N * D;
-  static_assert(!FUSED || CHM == 8, "the fused child compare holds one 16-row candidate tile");
+  const T* khead = static_cast<const T*>(fa.K) + (kFused ? (size_t)bh * N * D : 0);
+  const int h = kFused ? bh % fa.H : 0;
 
-  // the family table of this half wave: row 0 = stay, row 1 + c = child c
-  float acc[1 + CHM][CPL];
-#pragma unroll
-  for (int r = 0; r <= CHM; ++r)
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) acc[r][i] = 0.f;
-
-  // FUSED: the queue holds (key, family); bucket it by family, compare each
-  // group of 16 keys with its family's candidates, and leave the queue as
-  // (key, row) in family order, the code of every key written
-  auto child_step = [&](int qlen) {
-    constexpr int NT = 1;
-    using CT = ChildTile<T, D, NT>;
-    constexpr int KQ = CT::KQ;
-    using Frag = typename CT::Frag;
-    // at d = 64 the next group's key fragments stay in flight; at d = 128
-    // they load when they are used (the family table, the candidate rows and
-    // two sets of key fragments would pass the 128 registers of a lane)
-    constexpr bool kPrefetch = D == 64;
-    const int h = bh % fa.H;
-    const T* kh = static_cast<const T*>(fa.K) + (size_t)bh * N * D;
-    // thread and lane index through an empty asm statement: the LDS
-    // addresses below are formed here, not held (or spilled) from the start
-    int tq = tid, lq = lane;
-    asm volatile("" : "+v"(tq), "+v"(lq));
-    if (tq < kFamilies) L.hist[tq] = 0;
-    __syncthreads();
-    for (int e = tq; e < qlen; e += kAggThreads) atomicAdd(&L.hist[L.qrow[e]], 1);
-    __syncthreads();
-    if (wave == 0) {  // family starts and group starts (nfam <= 32 lanes)
-      const int lane = lq;
-      const int v = lane < nfam ? L.hist[lane] : 0;
-      const int gv = (v + 15) / 16;
-      const int incl = wave_incl_scan(v), gincl = wave_incl_scan(gv);
-      if (lane < nfam) {
-        L.fstart[lane] = incl - v;
-        L.fcursor[lane] = incl - v;
-        L.item_start[lane] = gincl - gv;
-      }
-      if (lane == nfam - 1) {
-        L.fstart[nfam] = incl;
-        L.item_start[nfam] = gincl;
-      }
+  // (family of this range, row) of a code: false if it belongs to another
+  // range. Rows: 0 the parent stays, 1 + x child x; flat: the parent's row.
+  auto locate = [&](int code, int& f, int& row) {
+    row = 0;
+    if constexpr (kFused) {
+      f = code - p0;
+    } else if constexpr (kFlat) {
+      f = (code >> 4) - p0;
+      row = code & 15;
+      if (code >= M0) f = -1;
+    } else {
+      const int x = code - M0;
+      f = (x < 0 ? code : x >> ch_shift) - p0;
+      row = x < 0 ? 0 : 1 + (x & (Ch - 1));
+      if (code >= Mtot) f = -1;
     }
-    __syncthreads();
-    for (int e = tid; e < qlen; e += kAggThreads)
-      L.skey[atomicAdd(&L.fcursor[L.qrow[e]], 1)] = L.qkey[e];
-    __syncthreads();
-    // each wave a contiguous run of groups (consecutive groups mostly share
-    // the family, whose candidate rows stay in registers)
-    const int g = lane / 16, c = lane % 16;
-    const int n_items = L.item_start[nfam];
-    const int per_wave = (n_items + kAggWaves - 1) / kAggWaves;
-    const int it_begin = wave * per_wave, it_end = min(n_items, it_begin + per_wave);
-    auto group_keys = [&](int f, int it, Frag (&kf)[KQ], int& pos, bool& valid) {
-      const int kb = L.fstart[f] + 16 * (it - L.item_start[f]);
-      valid = kb + c < L.fstart[f + 1];
-      pos = valid ? kb + c : kb;
-      child_key<T, D, NT>(kh + (size_t)L.skey[pos] * D, g, kf);
-    };
-    Frag cf[NT][KQ];
-    f32x4 cn[NT];
-    Frag kf[KQ];
-    int cur_f = -1, f = 0, pos = 0;
-    bool valid = false;
-    if (it_begin < it_end) {
-      while (L.item_start[f + 1] <= it_begin) ++f;  // wave-uniform
-      group_keys(f, it_begin, kf, pos, valid);
-    }
-    for (int it = it_begin; it < it_end; ++it) {
-      Frag kn[KQ];
-      int fn = f, pos_n = 0;
-      bool valid_n = false;
-      if (it + 1 < it_end) {
-        while (L.item_start[fn + 1] <= it + 1) ++fn;  // wave-uniform
-        if constexpr (kPrefetch) group_keys(fn, it + 1, kn, pos_n, valid_n);
-      }
-      if constexpr (!kPrefetch) {
-        if (it > it_begin) group_keys(f, it, kf, pos, valid);
-      }
-      const int p = p0 + f;
-      if (f != cur_f) {
-        child_rows<T, D, NT>(static_cast<const T*>(fa.Cp), static_cast<const T*>(fa.Cc), h, M0,
-                             Ch, p, g, c, cf, cn);
-        cur_f = f;
-      }
-      const int r = child_pick<T, D, NT>(cf, cn, kf, Ch, g, c);
-      if (g == 0 && valid) {
-        const int key = L.skey[pos];
-        fa.code_idx[(size_t)bh * N + key] = r > 0 ? M0 + p * Ch + r - 1 : p;
-        L.qkey[pos] = key;
-        L.qrow[pos] = (uint16_t)(f * (1 + Ch) + r);
-      }
-      if constexpr (kPrefetch) {
+    return (unsigned)f < (unsigned)nfam && code >= 0;
+  };
+  // f(key, code) for the keys [k0, k1): 8 codes in flight per lane
+  auto scan = [&](int k0, int k1, auto&& f) {
+    constexpr int kStep = 8;
+    for (int b = k0 + tid; b < k1; b += kStep * Cfg::kThreads) {
+      int cd[kStep];
 #pragma unroll
-        for (int kq = 0; kq < KQ; ++kq) kf[kq] = kn[kq];
-        pos = pos_n;
-        valid = valid_n;
+      for (int i = 0; i < kStep; ++i) {
+        const int j = b + i * Cfg::kThreads;
+        cd[i] = j < k1 ? codes[j] : -1;
       }
-      f = fn;
+#pragma unroll
+      for (int i = 0; i < kStep; ++i) f(b + i * Cfg::kThreads, cd[i]);
     }
-    __syncthreads();
   };
 
-  // 1. scan the head's codes and queue the keys of this range; bucket and
-  //    sum the queue when it would overflow and once the codes are exhausted
-  int qlen = 0;
-  int next[kCodesPerThread];
-  auto load_round = [&](int b, int (&dst)[kCodesPerThread]) {
-#pragma unroll
-    for (int k = 0; k < kCodesPerThread; ++k) {
-      const int j = b + k * kAggThreads + tid;
-      dst[k] = j < N ? codes[j] : -1;
-    }
-  };
-  load_round(0, next);
-  // family-local row of a code (or, FUSED, the family of a parent index);
-  // -1 outside this range
-  auto row_of = [&](int code) {
-    int r = -1;
-    if constexpr (FUSED) {  // the family; its row comes from the child compare
-      if (code >= p0 && code < p0 + nfam) r = code - p0;
-    } else if (code >= 0 && code < Mtot) {
-      // Ch is a power of two: child code M0 + p Ch + c
-      const int p = code < M0 ? code : (code - M0) >> ch_shift;
-      if (p >= p0 && p < p0 + nfam)
-        r = (p - p0) * (1 + Ch) + (code < M0 ? 0 : 1 + ((code - M0) & (Ch - 1)));
-    }
-    return r;
-  };
-  for (int base = 0;; base += kRound) {
-    const bool done = base >= N;
-    // this round's codes; their rows and ballots are taken again after a
-    // flush rather than kept in registers through it
-    int cur[kCodesPerThread];
-    int round_total = 0;
-    if (!done) {
-#pragma unroll
-      for (int k = 0; k < kCodesPerThread; ++k) cur[k] = next[k];
-#pragma unroll
-      for (int k = 0; k < kCodesPerThread; ++k) {
-        const unsigned long long mk = __ballot(row_of(cur[k]) >= 0);
-        if (lane == 0) L.wave_count[k][wave] = __popcll(mk);
-      }
-      __syncthreads();
-      if (wave == 0) {
-        const int tot = prefix128(&L.wave_count[0][0], &L.wave_off[0][0],
-                                  kCodesPerThread * kAggWaves, lane);
-        if (lane == 0) L.round_total = tot;
-      }
-      __syncthreads();
-      round_total = L.round_total;
-      load_round(base + kRound, next);  // prefetch the next round
-    }
-    // uniform across the workgroup
-    const bool flush = done ? qlen > 0 : qlen + round_total > kQueueCap;
-    if (flush) {
-      if constexpr (FUSED) child_step(qlen);
-      // as in child_step: indices through an empty asm statement
-      int tq = tid, lq = lane;
-      asm volatile("" : "+v"(tq), "+v"(lq));
-      for (int r = tq; r < rows; r += kAggThreads) L.hist[r] = 0;
-      __syncthreads();
-      for (int e = tq; e < qlen; e += kAggThreads) atomicAdd(&L.hist[L.qrow[e]], 1);
-      __syncthreads();
-      if (wave == 0) {  // exclusive scan of the row histogram
-        const int lane = lq;
-        int carry = 0;
-        for (int r0 = 0; r0 < rows; r0 += kWave) {
-          const int r = r0 + lane;
-          const int v = r < rows ? L.hist[r] : 0;
-          const int incl = wave_incl_scan(v);
-          if (r < rows) {
-            L.start[r] = carry + incl - v;
-            L.cursor[r] = carry + incl - v;
-            L.total[r] += v;
-          }
-          carry += last_lane(incl);
-        }
-        if (lane == 0) L.start[rows] = carry;
-      }
-      __syncthreads();
-      for (int e = tid; e < qlen; e += kAggThreads)
-        L.skey[atomicAdd(&L.cursor[L.qrow[e]], 1)] = L.qkey[e];
-      __syncthreads();
-      if (fam < nfam) {
-        // the family's keys, bucketed by row, in kInFlight<CHM, T> batches; the
-        // running row sum goes into the table when its row ends. The family
-        // index passes an empty asm statement: its row addresses are formed
-        // here, not held (or spilled) from the kernel start.
-        int fq = fam;
-        asm volatile("" : "+v"(fq));
-        const int r_begin = fq * (1 + Ch);
-        const int fb = L.start[r_begin], fe = L.start[r_begin + 1 + Ch];
-        // this half wave's share of the family's keys
-        const int kb = fb + (fe - fb) * part / SPLIT, ke = fb + (fe - fb) * (part + 1) / SPLIT;
-        int rr = 0;                          // current row of the family
-        int row_end = L.start[r_begin + 1];  // end of its bucket
-        float cur[CPL];
-#pragma unroll
-        for (int i = 0; i < CPL; ++i) cur[i] = 0.f;
-        // every table row takes cur or zero: a plain add per row keeps the
-        // table in registers (a conditional add on rr alone is turned into an
-        // indexed access to scratch memory)
-        auto close_row = [&]() {
-#pragma unroll
-          for (int r = 0; r <= CHM; ++r)
-#pragma unroll
-            for (int i = 0; i < CPL; ++i) acc[r][i] += r == rr ? cur[i] : 0.f;
-#pragma unroll
-          for (int i = 0; i < CPL; ++i) cur[i] = 0.f;
-        };
-        // a ring of kIF rows in flight: slot u holds key k0 + u; once it is
-        // summed it is refilled with key k0 + kIF + u, so kIF - 1 loads stay
-        // in flight while the rows are added. Keys past the share repeat its
-        // last key: the refills are unconditional, so the compiler's count
-        // of outstanding loads is exact and every wait leaves kIF - 1 of them
-        // in flight (a conditional refill makes it wait for more).
-        constexpr int kIF = kInFlight<CHM, T>;
-        auto row_of = [&](int k) {
-          return *reinterpret_cast<const Raw*>(vhead + (size_t)L.skey[min(k, ke - 1)] * D + sub * CPL);
-        };
-        Raw raw[kIF];
-        if (kb < ke) {
-#pragma unroll
-          for (int u = 0; u < kIF; ++u) raw[u] = row_of(kb + u);
-        }
-        for (int k0 = kb; k0 < ke; k0 += kIF) {
-#pragma unroll
-          for (int u = 0; u < kIF; ++u) {
-            if (k0 + u < ke) {
-              while (k0 + u >= row_end) {  // uniform within the half wave
-                close_row();
-                ++rr;
-                row_end = L.start[r_begin + rr + 1];
-              }
-              // the row is unpacked here, not where it was loaded: otherwise
-              // the compiler moves the unpacking next to the loads and waits
-              // for all of them there
-              pin_words(raw[u]);
-              const T* x = reinterpret_cast<const T*>(&raw[u]);
-#pragma unroll
-              for (int i = 0; i < CPL; ++i) cur[i] += to_f32(x[i]);
-            }
-            raw[u] = row_of(k0 + kIF + u);
-          }
-        }
-        if (kb < ke) close_row();
-      }
-      __syncthreads();
-      qlen = 0;
-      // this round's codes and the next round's are loaded again rather than
-      // held in registers through the flush
-      if (!done) {
-        load_round(base, cur);
-        load_round(base + kRound, next);
-      }
-    }
-    if (done) break;
-#pragma unroll
-    for (int k = 0; k < kCodesPerThread; ++k) {
-      asm volatile("" : "+v"(cur[k]));  // rows from the codes, not held through the flush
-      const int row = row_of(cur[k]);
-      const unsigned long long mk = __ballot(row >= 0);
-      if (row >= 0) {
-        const int slot = qlen + L.wave_off[k][wave] + bits_below(mk);
-        L.qkey[slot] = base + k * kAggThreads + tid;
-        L.qrow[slot] = (uint16_t)row;
-      }
-    }
-    qlen += round_total;
-    __syncthreads();
-  }
+  // ---- 1. keys per family ------------------------------------------------
+  if (tid < kMaxFamilies) L.hist[tid] = 0;
+  __syncthreads();
+  scan(0, N, [&](int, int code) {
+    int f, row;
+    if (locate(code, f, row)) atomicAdd(&L.hist[f], 1);
+  });
+  __syncthreads();
 
-  // 2. parent row = stay + children; write every row once, and the counts.
-  //    Packed aggregates (optional): the owner writes its children's octets
-  //    directly; the parents' octets (8 parents from 8 owners each) are put
-  //    together through LDS (the queue area is free now).
-  const PackedLayout PL = packed_layout(M0, Ch, D, (int)sizeof(T));
-  if constexpr (SPLIT > 1) {
-    // add the shares of parts 1 .. SPLIT-1 into part 0's table, row by row,
-    // in part order, through the free key queue
-    float* share = reinterpret_cast<float*>(L.qkey);  // [SPLIT - 1][FAM][D]
-    static_assert((SPLIT - 1) * FAM * D * 4 <= sizeof(L.qkey), "shares fit the key queue");
+  // The lane index through an empty asm statement: the addresses formed from
+  // it are computed where they are used, not hoisted out of the group loop and
+  // held (or spilled) through it.
+  auto hidden = [](int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+  };
+
+  // ---- a family's sums ---------------------------------------------------
+  // acc[nt][t][r]: row 4 g + r of tile nt at column VR::col(t, c); an[nt][r]
+  // the row's count
+  f32x4 acc[NT][CT], an[NT];
+  auto zero_acc = [&]() {
 #pragma unroll
-    for (int r = 0; r <= CHM; ++r) {
-      if (r <= Ch) {  // uniform
-        if (fam < nfam && part > 0) {
+    for (int nt = 0; nt < NT; ++nt) {
+      an[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int i = 0; i < CPL; ++i) share[((part - 1) * FAM + fam) * D + sub * CPL + i] = acc[r][i];
-        }
-        __syncthreads();
-        if (fam < nfam && part == 0) {
-#pragma unroll
-          for (int q = 1; q < SPLIT; ++q)
-#pragma unroll
-            for (int i = 0; i < CPL; ++i) acc[r][i] += share[((q - 1) * FAM + fam) * D + sub * CPL + i];
-        }
-        __syncthreads();
-      }
+      for (int t = 0; t < CT; ++t) acc[nt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-  }
-  float* pmean = reinterpret_cast<float*>(L.qkey);  // [FAM][D]
-  int* pcell = reinterpret_cast<int*>(pmean + FAM * D);  // [FAM] cell sizes
-  static_assert((kFamilies * D + kFamilies) * 4 <= sizeof(L.qkey), "parent means fit the key queue");
-  // child octets leave through a 1 KB staging area per family (in the free
-  // row and bucket queues), so that each store writes 16 consecutive bytes
-  // per lane, contiguous over the half wave
-  constexpr int kStageRows = 1024 / (8 * (int)sizeof(T));  // octet d-rows per pass
-  static_assert(kFamilies * 1024 <= sizeof(L.qrow) + sizeof(L.skey), "staging fits the queues");
-  static_assert(kStageRows % kFamLanes == 0 && D % kStageRows == 0, "whole passes");
-  T* stage = reinterpret_cast<T*>(reinterpret_cast<unsigned char*>(L.qrow) + fam * 1024);
+  };
+  // held row x of tile nt: its index among ROWS, or -1
+  auto held = [&](int nt, int x) {
+    if constexpr (kFlat) return x;
+    return nt == 0 ? (x <= 8 ? x : -1) : (x < 8 ? 9 + x : -1);
+  };
+  auto slot_sum = [&](int w) { return reinterpret_cast<float*>(lds_raw + Cfg::OFF_SLOT + w * Cfg::SLOT_BYTES); };
+  auto store_slot = [&]() {
+    const int lq = hidden(lane), g = lq / 16, c = lq % 16;
+    float* s = slot_sum(wave);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int x = held(nt, 4 * g + r);
+        if (x < 0) continue;
+#pragma unroll
+        for (int t = 0; t < CT; t += 4)
+          *reinterpret_cast<f32x4*>(&s[x * D + VR::col(t, c)]) =
+              f32x4{acc[nt][t][r], acc[nt][t + 1][r], acc[nt][t + 2][r], acc[nt][t + 3][r]};
+        if (c == 0) s[ROWS * D + x] = an[nt][r];
+      }
+  };
+  auto add_slot = [&](int w) {
+    const int lq = hidden(lane), g = lq / 16, c = lq % 16;
+    const float* s = slot_sum(w);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int x = held(nt, 4 * g + r);
+        if (x < 0) continue;
+#pragma unroll
+        for (int t = 0; t < CT; t += 4) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(&s[x * D + VR::col(t, c)]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[nt][t + i][r] += v[i];
+        }
+        an[nt][r] += s[ROWS * D + x];
+      }
+  };
+
   float* vb = Vbar ? Vbar + (size_t)bh * Mtot * D : nullptr;
   unsigned char* pk = packed ? packed + (size_t)bh * PL.bytes : nullptr;
   T* means = reinterpret_cast<T*>(pk);
   float* info = reinterpret_cast<float*>(pk + PL.info_off);
+  int32_t* nb = counts + (size_t)bh * Mtot;
   constexpr float kNegInf = -__builtin_inff();
   constexpr float kLn2 = 0.6931471805599453f;
-  if (fam < nfam && part == 0) {
-    const int p = p0 + fam;
-    const int* tot = &L.total[fam * (1 + Ch)];
-    float par[CPL];
+  auto ln_n = [&](float n) { return n > 0.f ? log2_hw(n) * kLn2 : kNegInf; };
+  // a wave's LDS writes are read by its other lanes: LDS operations of one
+  // wave complete in order
+  auto wave_lds_fence = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+
+  // writes every row of family f: sums, counts, its octets with their counts;
+  // the parent's mean and cell size go to LDS
+  auto write_family = [&](int f) {
+    const int lq = hidden(lane), g = lq / 16, c = lq % 16;
+    const int p = p0 + f;
+    unsigned char* st = lds_raw + Cfg::OFF_STAGE + wave * Cfg::STAGE_BYTES;
 #pragma unroll
-    for (int i = 0; i < CPL; ++i) par[i] = acc[0][i];
-    int ncell = tot[0];
+    for (int nt = 0; nt < NT; ++nt) {
+      // the code of row x, or -1
+      auto code_of = [&](int x) {
+        if constexpr (kFlat) return 16 * p + x < M0 ? 16 * p + x : -1;
+        return x < 8 ? (8 * nt + x < Ch ? M0 + p * Ch + 8 * nt + x : -1) : (x == 8 && nt == 0 ? p : -1);
+      };
+      float inv[4];
 #pragma unroll
-    for (int r = 1; r <= CHM; ++r) {
-      if (r <= Ch) {
-        if (vb) {
-          float* dst = vb + (size_t)(M0 + p * Ch + (r - 1)) * D + sub * CPL;
+      for (int r = 0; r < 4; ++r) {
+        const int code = code_of(4 * g + r);
+        const float n = an[nt][r];
+        inv[r] = n > 0.f ? 1.f / n : 0.f;
+        if (code >= 0) {
+          if (c == 0) nb[code] = (int)n;
+          if (vb) {
 #pragma unroll
-          for (int i = 0; i < CPL; i += 2)
-            *reinterpret_cast<float2*>(dst + i) = float2{acc[r][i], acc[r][i + 1]};
-        }
-#pragma unroll
-        for (int i = 0; i < CPL; ++i) par[i] += acc[r][i];
-        ncell += tot[r];
-      }
-    }
-    if (vb) {
-      float* dst = vb + (size_t)p * D + sub * CPL;
-#pragma unroll
-      for (int i = 0; i < CPL; i += 2) *reinterpret_cast<float2*>(dst + i) = float2{par[i], par[i + 1]};
-    }
-    if (pk) {
-      const float pinv = ncell > 0 ? 1.f / (float)ncell : 0.f;
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) pmean[fam * D + sub * CPL + i] = par[i] * pinv;
-      if (sub == 0) pcell[fam] = ncell;
-      // this parent's child octets: [CO][D][8], and their info
-#pragma unroll
-      for (int j = 0; j < (CHM + 7) / 8; ++j) {
-        if (j < PL.CO) {
-          const int o = PL.PO + p * PL.CO + j;
-          float inv[8];
-#pragma unroll
-          for (int sl = 0; sl < 8; ++sl) {
-            const int c = 8 * j + sl;
-            const int n = c < Ch ? tot[1 + c] : 0;
-            inv[sl] = n > 0 ? 1.f / (float)n : 0.f;
-          }
-          // pass q: the lanes holding d-rows q R .. q R + R - 1 (R =
-          // kStageRows) put them in the staging area, then lane sub stores
-          // d-rows q R + sub + 32 t
-#pragma unroll
-          for (int q = 0; q < D / kStageRows; ++q) {
-#pragma unroll
-            for (int i = 0; i < CPL; ++i) {
-              const int dr = sub * CPL + i - q * kStageRows;
-              if (dr < 0 || dr >= kStageRows) continue;
-              float v[8];
-#pragma unroll
-              for (int sl = 0; sl < 8; ++sl) {
-                float a = 0.f;
-#pragma unroll
-                for (int r = 1; r <= CHM; ++r)
-                  if (r == 1 + 8 * j + sl) a = acc[r][i];
-                v[sl] = a * inv[sl];
-              }
-              T* sd = stage + dr * 8;
-              if constexpr (Elem<T>::kBf16) {
-                bf16x8 w = {(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3],
-                            (bf16)v[4], (bf16)v[5], (bf16)v[6], (bf16)v[7]};
-                *reinterpret_cast<bf16x8*>(sd) = w;
-              } else {
-                reinterpret_cast<float4*>(sd)[0] = float4{v[0], v[1], v[2], v[3]};
-                reinterpret_cast<float4*>(sd)[1] = float4{v[4], v[5], v[6], v[7]};
-              }
-            }
-            // the half wave's own LDS writes and reads stay in order
-            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int t = 0; t < kStageRows / kFamLanes; ++t) {
-              const int dr = sub + kFamLanes * t;
-              T* dst = means + ((size_t)o * D + q * kStageRows + dr) * 8;
-              if constexpr (Elem<T>::kBf16) {
-                *reinterpret_cast<bf16x8*>(dst) = *reinterpret_cast<const bf16x8*>(stage + dr * 8);
-              } else {
-                reinterpret_cast<float4*>(dst)[0] = reinterpret_cast<const float4*>(stage + dr * 8)[0];
-                reinterpret_cast<float4*>(dst)[1] = reinterpret_cast<const float4*>(stage + dr * 8)[1];
-              }
-            }
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            __builtin_amdgcn_wave_barrier();
-          }
-          // lane sub < 16 writes info slot sub: n (slots 0..7), ln n (8..15)
-          if (sub < 16) {
-            const int c = 8 * j + (sub & 7);
-            const int n = c < Ch ? tot[1 + c] : 0;
-            info[(size_t)o * 16 + sub] =
-                sub < 8 ? (float)n : (n > 0 ? log2_hw((float)n) * kLn2 : kNegInf);
+            for (int t = 0; t < CT; t += 4)
+              *reinterpret_cast<f32x4*>(&vb[(size_t)code * D + VR::col(t, c)]) =
+                  f32x4{acc[nt][t][r], acc[nt][t + 1][r], acc[nt][t + 2][r], acc[nt][t + 3][r]};
           }
         }
       }
-    }
-  }
-  __syncthreads();
-  if (pk) {
-    // the parent octets of this range (the last range also writes the padding
-    // octets, the first one the empty octet)
-    const int o_begin = p0 / 8;
-    const int o_end = (p0 + nfam >= M0) ? PL.PO : (p0 + nfam) / 8;
-    const int nrow = (o_end - o_begin) * D;
-    for (int i = tid; i < nrow; i += kAggThreads) {
-      const int o = o_begin + i / D, d = i % D;
-      float v[8];
+      if (!pk) continue;
+      if (!kFlat && nt == 0 && g == 2) {  // row 8: the parent
 #pragma unroll
-      for (int sl = 0; sl < 8; ++sl) {
-        const int q = 8 * o + sl - p0;
-        v[sl] = q < nfam ? pmean[q * D + d] : 0.f;
+        for (int t = 0; t < CT; ++t) pmean[f * D + VR::col(t, c)] = (T)(acc[0][t][0] * inv[0]);
+        if (c == 0) L.cell[f] = an[0][0];
       }
-      T* dst = means + ((size_t)o * D + d) * 8;
-      if constexpr (Elem<T>::kBf16) {
-        bf16x8 w = {(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3],
-                    (bf16)v[4], (bf16)v[5], (bf16)v[6], (bf16)v[7]};
-        *reinterpret_cast<bf16x8*>(dst) = w;
-      } else {
-        reinterpret_cast<float4*>(dst)[0] = float4{v[0], v[1], v[2], v[3]};
-        reinterpret_cast<float4*>(dst)[1] = float4{v[4], v[5], v[6], v[7]};
+      // rows 0..7 (flat: and 8..15) through the staging area, so that each
+      // store is 16 consecutive bytes per lane over the whole octet. 16-byte
+      // units are XOR-swizzled so that the lanes' columns hit distinct banks.
+      constexpr int kUnits = Cfg::OCT_BYTES / 16;  // per octet
+      auto swz = [&](int u) { return u ^ ((u >> 3) & 7); };
+      const bool mine = kFlat || g < 2;
+      const int oct = kFlat ? g / 2 : 0;  // octet of the staging area
+      if (mine) {
+        unsigned char* so = st + oct * Cfg::OCT_BYTES;
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+          const int col = VR::col(t, c);
+          if constexpr (kB) {
+            const bf16x4 o = {(bf16)(acc[nt][t][0] * inv[0]), (bf16)(acc[nt][t][1] * inv[1]),
+                              (bf16)(acc[nt][t][2] * inv[2]), (bf16)(acc[nt][t][3] * inv[3])};
+            *reinterpret_cast<bf16x4*>(so + 16 * swz(col) + 8 * (g & 1)) = o;
+          } else {
+            const f32x4 o = {acc[nt][t][0] * inv[0], acc[nt][t][1] * inv[1],
+                             acc[nt][t][2] * inv[2], acc[nt][t][3] * inv[3]};
+            *reinterpret_cast<f32x4*>(so + 16 * swz(2 * col + (g & 1))) = o;
+          }
+        }
+        if (c == 0) {
+          const int o = kFlat ? 2 * p + oct : PL.PO + p * PL.CO + nt;
+          f32x4 n4, l4;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            n4[r] = an[nt][r];
+            l4[r] = ln_n(an[nt][r]);
+          }
+          *reinterpret_cast<f32x4*>(&info[(size_t)o * 16 + 4 * (g & 1)]) = n4;
+          *reinterpret_cast<f32x4*>(&info[(size_t)o * 16 + 8 + 4 * (g & 1)]) = l4;
+        }
+      }
+      wave_lds_fence();
+      constexpr int kOcts = kFlat ? 2 : 1;
+#pragma unroll
+      for (int i = 0; i < kOcts * kUnits / kWave; ++i) {
+        const int u = lq + kWave * i;
+        const int o = kFlat ? 2 * p + u / kUnits : PL.PO + p * PL.CO + nt;
+        const uint4 v = *reinterpret_cast<const uint4*>(st + (u / kUnits) * Cfg::OCT_BYTES + 16 * swz(u % kUnits));
+        *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(means) + (size_t)o * Cfg::OCT_BYTES +
+                                  16 * (u % kUnits)) = v;
+      }
+      wave_lds_fence();
+    }
+  };
+
+  // ---- 2. and 3. in batches of families that fit the key list ------------
+  for (int f0 = 0; f0 < nfam;) {
+    // families f0 .. f1 - 1 (uniform): each at least one group, so that the
+    // wave of its first group writes it, empty or not
+    if (wave == 0) {
+      const int n = lane >= f0 && lane < nfam ? L.hist[lane < kMaxFamilies ? lane : 0] : 0;
+      const int ng = lane >= f0 && lane < nfam ? max(1, (n + kGroup - 1) / kGroup) : 0;
+      const int incl = wave_incl_scan(ng);
+      if (lane < nfam) L.gstart[lane] = incl - ng;
+      if (lane == nfam - 1) L.gstart[nfam] = incl;
+      if (lane < kMaxFamilies) L.cursor[lane] = 0;
+    }
+    __syncthreads();
+    int f1 = nfam;
+    while (f1 > f0 + 1 && L.gstart[f1] * kGroup > cap) --f1;
+    // a family past the list: segments of the head that fit whatever they hold
+    const bool giant = L.gstart[f1] * kGroup > cap;
+    zero_acc();
+    for (int s0 = 0; s0 < N; s0 += giant ? cap : N) {
+      const int s1 = giant ? min(N, s0 + cap) : N;
+      scan(s0, s1, [&](int key, int code) {
+        int f, row;
+        if (locate(code, f, row) && f >= f0 && f < f1) {
+          const int k = atomicAdd(&L.cursor[f], 1);
+          // key k of a group lies in slot 8 (k % 4) + k / 4: lane group g
+          // reads slots 8 g .. 8 g + 7, i.e. keys g, 4 + g, 8 + g, ...
+          const int slot = L.gstart[f] * kGroup + (k & ~31) + (k & 3) * 8 + ((k & 31) >> 2);
+          list[slot] = (uint32_t)key | (kFused ? 0u : (uint32_t)row << 24);
+        }
+      });
+      __syncthreads();
+      const int seg_n = L.cursor[f0];  // giant: keys of this segment
+      const int NG = giant ? (seg_n + kGroup - 1) / kGroup : L.gstart[f1];
+      const int gb = (int)((long long)NG * wave / W), ge = (int)((long long)NG * (wave + 1) / W);
+
+      if (gb < ge) {
+        using CTile = ChildTile<T, D, NT>;
+        constexpr int KQ = CTile::KQ;
+        using Frag = typename CTile::Frag;
+        Frag kf[kFused ? 2 : 1][KQ];   // key rows: two tiles of 16 keys
+        Frag cf[kFused ? NT : 1][KQ];  // the family's candidate rows
+        f32x4 cn[kFused ? NT : 1];
+        VR vr[8];
+        uint32_t ent[8];    // list entries 8 g .. 8 g + 7 (key, row)
+        uint32_t kent[2];   // FUSED: entries of compare columns c
+        int f = f0;
+        while (!giant && L.gstart[f + 1] <= gb) ++f;  // wave-uniform
+        int n = 0;  // keys of the current group
+        auto group_n = [&](int ff, int it) {
+          const int tot = giant ? seg_n : L.hist[ff];
+          return min(kGroup, tot - kGroup * (it - (giant ? 0 : L.gstart[ff])));
+        };
+        // list entries of group it (n keys): slots past n repeat the group's
+        // first key (an empty group: key 0)
+        auto read_entries = [&](int it, int nk) {
+          const uint4* q = reinterpret_cast<const uint4*>(&list[it * kGroup + 8 * g]);
+          const uint4 a = q[0], b = q[1];
+          ent[0] = a.x;
+          ent[1] = a.y;
+          ent[2] = a.z;
+          ent[3] = a.w;
+          ent[4] = b.x;
+          ent[5] = b.y;
+          ent[6] = b.z;
+          ent[7] = b.w;
+          if constexpr (kFused) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) kent[t] = list[it * kGroup + 8 * (c / 4) + c % 4 + 4 * t];
+          }
+          if (nk < kGroup) {
+            const uint32_t e0 = nk > 0 ? __builtin_amdgcn_readfirstlane(ent[0]) : 0u;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) ent[j] = 4 * j + g < nk ? ent[j] : e0;
+            if constexpr (kFused) {
+#pragma unroll
+              for (int t = 0; t < 2; ++t) kent[t] = 4 * (c % 4 + 4 * t) + c / 4 < nk ? kent[t] : e0;
+            }
+          }
+        };
+        auto load_k = [&]() {
+          if constexpr (kFused) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+              if constexpr (kB) {  // as ValRow::load_key
+                const uint32_t off = kent[t] * (uint32_t)(D * sizeof(T)) + 16u * g;
+                child_key<T, D, NT>(reinterpret_cast<const T*>(
+                                        reinterpret_cast<const unsigned char*>(khead) + (size_t)off),
+                                    0, kf[t]);
+              } else {
+                child_key<T, D, NT>(khead + (size_t)kent[t] * D, g, kf[t]);
+              }
+            }
+          }
+        };
+        auto load_v = [&]() {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) vr[j].load_key(vhead, ent[j] & 0xFFFFFFu, c);
+        };
+        auto load_rows = [&](int ff) {
+          if constexpr (kFused)
+            child_rows_load<T, D, NT>(static_cast<const T*>(fa.Cp), static_cast<const T*>(fa.Cc),
+                                      h, M0, Ch, p0 + ff, g, c, cf);
+        };
+        n = group_n(f, gb);
+        read_entries(gb, n);
+        load_rows(f);
+        load_k();
+        load_v();
+        bool fresh = true;              // candidate rows just loaded
+        bool whole = giant ? false : L.gstart[f] >= gb;  // the family began in this run
+
+        for (int it = gb; it < ge; ++it) {
+          const bool last = !giant && L.gstart[f + 1] == it + 1;  // of the family
+          const int fn = last ? f + 1 : f;
+          const bool more = it + 1 < ge;
+          // the 32 keys' row bits, two per word: bit x is accumulator row x
+          uint32_t oh[NT][4];
+          uint32_t kcur[2] = {0, 0};
+          int rk[2] = {0, 0};
+          if constexpr (kFused) {
+            if (fresh) child_rows_finish<T, D, NT>(g, cf, cn);
+            rk[0] = child_pick<T, D, NT>(cf, cn, kf[0], Ch, g, c);
+            if (n > 16) rk[1] = child_pick<T, D, NT>(cf, cn, kf[1], Ch, g, c);
+            if (g == 0) {
+#pragma unroll
+              for (int t = 0; t < 2; ++t) {
+                const bool valid = 4 * (c % 4 + 4 * t) + c / 4 < n;
+                const uint32_t bits = (1u << rk[t]) >> 1;  // children; none if it stays
+                const int slot = 8 * (c / 4) + c % 4 + 4 * t;
+                L.onehot[wave][0][slot] = (uint16_t)(valid ? (bits & 0xFFu) | 0x100u : 0u);
+                if constexpr (NT == 2) L.onehot[wave][1][slot] = (uint16_t)(valid ? bits >> 8 : 0u);
+                kcur[t] = valid ? kent[t] : 0xFFFFFFFFu;
+              }
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+              const uint4 q = *reinterpret_cast<const uint4*>(&L.onehot[wave][nt][8 * g]);
+              oh[nt][0] = q.x;
+              oh[nt][1] = q.y;
+              oh[nt][2] = q.z;
+              oh[nt][3] = q.w;
+            }
+          } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              uint32_t w0[NT], w1[NT];
+              auto bits_of = [&](int j, uint32_t (&w)[NT]) {
+                const bool valid = 4 * j + g < n;
+                const uint32_t row = ent[j] >> 24;
+                if constexpr (kFlat) {
+                  w[0] = valid ? 1u << row : 0u;
+                } else {
+                  const uint32_t b = (1u << row) >> 1;
+                  w[0] = valid ? (b & 0xFFu) | 0x100u : 0u;
+                  if constexpr (NT == 2) w[1] = valid ? b >> 8 : 0u;
+                }
+              };
+              bits_of(2 * q, w0);
+              bits_of(2 * q + 1, w1);
+#pragma unroll
+              for (int nt = 0; nt < NT; ++nt) oh[nt][q] = w0[nt] | (w1[nt] << 16);
+            }
+          }
+          // the next group: its entries, and (FUSED) its candidate and key rows
+          const int nn = more ? group_n(giant ? f : fn, it + 1) : 0;
+          const int itn = more ? it + 1 : it;
+          read_entries(itn, nn);
+          if constexpr (kFused) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (last && more) load_rows(fn);
+            load_k();
+            __builtin_amdgcn_sched_barrier(0);
+            if (g == 0) {
+#pragma unroll
+              for (int t = 0; t < 2; ++t) {
+                if (kcur[t] == 0xFFFFFFFFu) continue;
+                const int p = p0 + f;
+                fa.code_idx[(size_t)bh * N + kcur[t]] = rk[t] > 0 ? M0 + p * Ch + rk[t] - 1 : p;
+              }
+            }
+          }
+          // sums^T += onehot . V (an empty family's only group: nothing)
+          if (n > 0) {
+            if constexpr (kB) {
+              bf16x8 a[NT];
+#pragma unroll
+              for (int nt = 0; nt < NT; ++nt) {
+                uint32_t w[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)  // bit c of both halves, as bf16 ones
+                  w[q] = __umul24((oh[nt][q] >> c) & 0x00010001u, 0x3F80u);
+                __builtin_memcpy(&a[nt], w, 16);
+              }
+#pragma unroll
+              for (int t = 0; t < CT; ++t) {
+                uint32_t w[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)  // keys 2q, 2q + 1 at the lane's column t
+                  w[q] = __builtin_amdgcn_perm(vr[2 * q + 1].w[t / 2], vr[2 * q].w[t / 2],
+                                               t % 2 ? 0x07060302u : 0x05040100u);
+                bf16x8 b;
+                __builtin_memcpy(&b, w, 16);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[nt][t] = mfma_bf16(a[nt], b, acc[nt][t]);
+              }
+              const bf16x8 ones = {(bf16)1.f, (bf16)1.f, (bf16)1.f, (bf16)1.f,
+                                   (bf16)1.f, (bf16)1.f, (bf16)1.f, (bf16)1.f};
+#pragma unroll
+              for (int nt = 0; nt < NT; ++nt) an[nt] = mfma_bf16(a[nt], ones, an[nt]);
+            } else {
+#pragma unroll
+              for (int j = 0; j < 8; ++j) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                  const float a = (float)((oh[nt][j / 2] >> (c + 16 * (j % 2))) & 1u);
+#pragma unroll
+                  for (int t = 0; t < CT; ++t)
+                    acc[nt][t] = mfma_f32(a, __uint_as_float(vr[j].w[t]), acc[nt][t]);
+                  an[nt] = mfma_f32(a, 1.f, an[nt]);
+                }
+              }
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          load_v();
+          __builtin_amdgcn_sched_barrier(0);
+          if (last) {
+            if (whole) write_family(f);
+            else store_slot();
+            zero_acc();
+            whole = true;
+          }
+          fresh = last;
+          f = fn;
+          n = nn;
+        }
+        // a family that goes on in the next wave's run, begun in an earlier
+        // one's: its part goes to the slot too (giant: after the last segment)
+        if (!giant && f < f1 && !whole && L.gstart[f + 1] > ge) store_slot();
+      }
+      if (giant) {
+        __syncthreads();
+        if (tid == 0) L.cursor[f0] = 0;
+        __syncthreads();
       }
     }
-    for (int i = tid; i < (o_end - o_begin) * 16; i += kAggThreads) {
-      const int o = o_begin + i / 16, sl = i % 16;
-      const int q = 8 * o + (sl & 7) - p0;
-      const int n = q < nfam ? pcell[q] : 0;
-      info[(size_t)o * 16 + sl] =
-          sl < 8 ? (float)n : (n > 0 ? log2_hw((float)n) * kLn2 : kNegInf);
+    if (giant) {
+      if (wave > 0) store_slot();
+      __syncthreads();
+      if (wave == 0) {
+        for (int w = 1; w < W; ++w) add_slot(w);
+        write_family(f0);
+      }
+      __syncthreads();
+    } else {
+      __syncthreads();
+      // the wave that holds the first, but not the last, group of a family
+      const int NG = L.gstart[f1];
+      auto run_end = [&](int w) { return (int)((long long)NG * (w + 1) / W); };
+      const int gb = (int)((long long)NG * wave / W), ge = run_end(wave);
+      if (gb < ge) {
+        int f = f0;
+        while (L.gstart[f + 1] < ge) ++f;  // the family of the run's last group
+        if (L.gstart[f + 1] > ge && L.gstart[f] >= gb) {
+          for (int w = wave + 1; w < W; ++w) {
+            if (run_end(w) > run_end(w - 1)) add_slot(w);
+            if (run_end(w) >= L.gstart[f + 1]) break;
+          }
+          write_family(f);
+        }
+      }
+      __syncthreads();
     }
-    if (p0 == 0) {  // the empty octet
-      for (int i = tid; i < D * 8; i += kAggThreads) means[(size_t)PL.zero_oct * D * 8 + i] = T(0.f);
-      if (tid < 16) info[(size_t)PL.zero_oct * 16 + tid] = tid < 8 ? 0.f : kNegInf;
+    f0 = f1;
+  }
+
+  // ---- parent octets (flat: written above) ---------------------------------
+  if (!pk) return;
+  if constexpr (!kFlat) {
+    const int p_end = p0 + nfam >= M0 ? 8 * PL.PO : p0 + nfam;  // the last range: the padding too
+    if (F % 8 == 0) {
+      const int o0 = p0 / 8;
+      for (int i = tid; i < (p_end / 8 - o0) * D; i += Cfg::kThreads) {
+        const int o = i / D, d = i % D;
+        T v[8];
+#pragma unroll
+        for (int sl = 0; sl < 8; ++sl) v[sl] = 8 * o + sl < nfam ? pmean[(8 * o + sl) * D + d] : T(0.f);
+        uint4* dst = reinterpret_cast<uint4*>(means + ((size_t)(o0 + o) * D + d) * 8);
+#pragma unroll
+        for (int q = 0; q < (int)sizeof(T) / 2; ++q) {
+          uint4 x;
+          __builtin_memcpy(&x, reinterpret_cast<const unsigned char*>(v) + 16 * q, 16);
+          dst[q] = x;
+        }
+      }
+    } else {  // part of an octet: this range's slots
+      for (int i = tid; i < (p_end - p0) * D; i += Cfg::kThreads) {
+        const int q = i / D, d = i % D, p = p0 + q;
+        means[((size_t)(p / 8) * D + d) * 8 + p % 8] = q < nfam ? pmean[q * D + d] : T(0.f);
+      }
+    }
+    for (int q = tid; q < p_end - p0; q += Cfg::kThreads) {
+      const int p = p0 + q;
+      const float n = q < nfam ? L.cell[q] : 0.f;
+      info[(size_t)(p / 8) * 16 + p % 8] = n;
+      info[(size_t)(p / 8) * 16 + 8 + p % 8] = ln_n(n);
     }
   }
-  int32_t* nb = counts + (size_t)bh * Mtot;
-  for (int f = tid; f < nfam; f += kAggThreads) {
-    const int* tot = &L.total[f * (1 + Ch)];
-    int cell = 0;
-    for (int c = 0; c <= Ch; ++c) cell += tot[c];
-    nb[p0 + f] = cell;
-    for (int c = 0; c < Ch; ++c) nb[M0 + (p0 + f) * Ch + c] = tot[1 + c];
+  if (p0 == 0) {  // the empty octet
+    for (int i = tid; i < D * 8; i += Cfg::kThreads) means[(size_t)PL.zero_oct * D * 8 + i] = T(0.f);
+    if (tid < 16) info[(size_t)PL.zero_oct * 16 + tid] = tid < 8 ? 0.f : kNegInf;
   }
 }
 
-template <typename T, int D, int CHM, int SPLIT, bool FUSED>
-hipError_t launch_aggregate_dcs(int BH, int N, int M0, int Ch, const void* V,
+// Families per workgroup: the most (up to 32) that still give every CU a
+// workgroup. A workgroup scans all codes of its head, so fewer families per
+// workgroup cost scanning; idle CUs cost more.
+inline int families_per_workgroup(long long BH, int n_fam, int cus) {
+  int F = kMaxFamilies;
+  while (F > 1 && BH * ((n_fam + F - 1) / F) < cus) F /= 2;
+  return F;
+}
+
+template <typename T, int D, int NT, int MODE>
+hipError_t launch_aggregate_cfg(int BH, int N, int M0, int Ch, const void* V,
                                 const int32_t* code_idx, float* Vbar, int32_t* counts,
                                 void* packed, const FusedArgs& fa, hipStream_t stream) {
-  // one range of kFamilies / SPLIT parents per workgroup: ranges start at
-  // multiples of 8 parents, so each packed octet of parent means is written
-  // by one workgroup
-  constexpr int FAM = kFamilies / SPLIT;
-  static_assert(FAM % 8 == 0, "parent octets are assembled by one workgroup");
-  static_assert(kRound <= kQueueCap, "one round of codes fits the queue");
-  const int ranges = (M0 + FAM - 1) / FAM;
-  const int lds = (int)sizeof(AggLds);
-  constexpr int chm_i = CHM == 0 ? 0 : CHM == 8 ? 1 : 2;
-  constexpr int split_i = SPLIT == 1 ? 0 : SPLIT == 2 ? 1 : 2;
-  constexpr int slot = (FUSED ? 128 : 64) +
-                       (((Elem<T>::kBf16 ? 0 : 1) * 2 + (D == 128 ? 1 : 0)) * 3 + chm_i) * 3 +
-                       split_i;
-  hipError_t e =
-      ensure_dynamic_lds((const void*)aggregate_kernel<T, D, CHM, SPLIT, FUSED>, lds, slot);
-  if (e != hipSuccess) return e;
-  const long long grid = (long long)BH * ranges;
-  if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((aggregate_kernel<T, D, CHM, SPLIT, FUSED>), dim3((unsigned)grid),
-                     dim3(kAggThreads), lds, stream, static_cast<const T*>(V), code_idx, Vbar,
-                     counts, static_cast<unsigned char*>(packed), N, M0, Ch, ranges, fa);
-  return hipGetLastError();
-}
-
-// Half waves per family. Each workgroup scans all codes of its head, so
-// splitting a family over more half waves (more, smaller workgroups) costs
-// scanning; it pays when some CUs would have no workgroup (few heads, few
-// parents) and either one half wave per family would walk a long chain of
-// value loads (at least 256 keys per parent) or the head's codes are one
-// scan round (then the extra scanning is that one round). Then the fewest
-// half waves (2 or 4) that give every CU a workgroup.
-template <typename T, int D, int CHM, bool FUSED>
-hipError_t launch_aggregate_dc(int BH, int N, int M0, int Ch, const void* V,
-                               const int32_t* code_idx, float* Vbar, int32_t* counts,
-                               void* packed, const FusedArgs& fa, hipStream_t stream) {
+  using Cfg = AggCfg<T, D, NT, MODE>;
   DeviceInfo dev;
   hipError_t e = device_info(&dev);
   if (e != hipSuccess) return e;
-  const long long cus = dev.cus > 1 ? dev.cus : 1;
-  auto grid = [&](int split) {
-    const int fam = kFamilies / split;
-    return (long long)BH * ((M0 + fam - 1) / fam);
-  };
-  const bool long_chains = (long long)N >= 256LL * M0;
-  if ((!long_chains && N > kRound) || grid(1) >= cus)
-    return launch_aggregate_dcs<T, D, CHM, 1, FUSED>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
-                                                     packed, fa, stream);
-  if (grid(2) >= cus)
-    return launch_aggregate_dcs<T, D, CHM, 2, FUSED>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
-                                                     packed, fa, stream);
-  return launch_aggregate_dcs<T, D, CHM, 4, FUSED>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
-                                                   packed, fa, stream);
+  const int n_fam = Cfg::kFlat ? packed_layout(M0, Ch, D, (int)sizeof(T)).PO / 2 : M0;
+  const int F = families_per_workgroup(BH, n_fam, dev.cus > 1 ? dev.cus : 1);
+  const int ranges = (n_fam + F - 1) / F;
+  const long long grid = (long long)BH * ranges;
+  if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;
+  // the key list takes the rest of the LDS that one workgroup may use, and
+  // no more than the head's keys with every family's last group padded
+  const int room = (dev.lds_max - Cfg::off_list(F)) / (4 * kGroup) * kGroup;
+  const long long most = ((long long)N + (long long)F * kGroup + kGroup - 1) / kGroup * kGroup;
+  const int cap = (int)std::min<long long>(room, most);
+  if (cap < F * kGroup) return hipErrorInvalidConfiguration;
+  const int lds = Cfg::off_list(F) + 4 * cap;
+  constexpr int slot = 64 + ((((Elem<T>::kBf16 ? 0 : 1) * 2 + (D == 128 ? 1 : 0)) * 2 + (NT - 1)) * 3 + MODE);
+  e = ensure_dynamic_lds((const void*)aggregate_kernel<T, D, NT, MODE>, lds, slot);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((aggregate_kernel<T, D, NT, MODE>), dim3((unsigned)grid), dim3(Cfg::kThreads),
+                     lds, stream, static_cast<const T*>(V), code_idx, Vbar, counts,
+                     static_cast<unsigned char*>(packed), N, M0, Ch, F, ranges, cap, fa);
+  return hipGetLastError();
 }
 
 template <typename T, int D>
@@ -672,15 +738,15 @@ hipError_t launch_aggregate_d(int BH, int N, int M0, int Ch, const void* V,
                               const int32_t* code_idx, float* Vbar, int32_t* counts,
                               void* packed, hipStream_t stream) {
   const FusedArgs none{};
-  if (Ch == 0)  // flat codebook: a family is one parent
-    return launch_aggregate_dc<T, D, 0, false>(BH, N, M0, Ch, V, code_idx, Vbar, counts, packed,
-                                               none, stream);
+  if (Ch == 0)
+    return launch_aggregate_cfg<T, D, 1, kAggFlat>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
+                                                   packed, none, stream);
   if (Ch <= 8)
-    return launch_aggregate_dc<T, D, 8, false>(BH, N, M0, Ch, V, code_idx, Vbar, counts, packed,
-                                               none, stream);
+    return launch_aggregate_cfg<T, D, 1, kAggCodes>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
+                                                    packed, none, stream);
   if (Ch <= 16)
-    return launch_aggregate_dc<T, D, 16, false>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
-                                                packed, none, stream);
+    return launch_aggregate_cfg<T, D, 2, kAggCodes>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
+                                                    packed, none, stream);
   return hipErrorInvalidValue;
 }
 
@@ -696,32 +762,43 @@ hipError_t launch_aggregate(int BH, int N, int d, int M0, int Ch, const void* V,
 }
 
 // Alg. 1 in two launches: the parent assignment (it reads K once and writes
-// parent_idx), then the fused child compare + aggregation (bf16, 1 <= Ch <=
-// 8). Ch = 0 (the parent is the code), Ch = 16 (two candidate tiles) and fp32
-// (its fragments, the family table and the candidate rows pass the registers
-// of a 1024-thread workgroup) take the parent and child kernels of the
-// assignment and then the plain aggregation.
+// parent_idx), then the fused child compare + aggregation. Ch = 0 (the parent
+// is the code) and fp32 with Ch = 16 at d = 128 (the candidate rows, the sums
+// and the key and value rows of a group pass the 256 registers of a lane)
+// take the assignment and then the plain aggregation.
+template <typename T, int D>
+hipError_t launch_assign_aggregate_d(int BH, int H, int N, int M0, int Ch, const void* K,
+                                     const void* V, const void* Cp, const void* Cc,
+                                     int32_t* parent_idx, int32_t* code_idx, float* Vbar,
+                                     int32_t* counts, void* packed, hipStream_t stream) {
+  constexpr bool kWide = Elem<T>::kBf16 || D == 64;  // Ch = 16 fused
+  const bool fused = Ch >= 1 && (Ch <= 8 || kWide);
+  hipError_t e = launch_assign<T, D>(BH, H, N, M0, Ch, K, Cp, Cc, parent_idx, code_idx, !fused, stream);
+  if (e != hipSuccess) return e;
+  if (!fused)
+    return launch_aggregate_d<T, D>(BH, N, M0, Ch, V, code_idx, Vbar, counts, packed, stream);
+  const FusedArgs fa{K, Cp, Cc, code_idx, H};
+  if (Ch <= 8)
+    return launch_aggregate_cfg<T, D, 1, kAggFused>(BH, N, M0, Ch, V, parent_idx, Vbar, counts,
+                                                    packed, fa, stream);
+  if constexpr (kWide)
+    return launch_aggregate_cfg<T, D, 2, kAggFused>(BH, N, M0, Ch, V, parent_idx, Vbar, counts,
+                                                    packed, fa, stream);
+  return hipErrorInvalidValue;  // not reached
+}
+
 template <typename T>
 hipError_t launch_assign_aggregate(int BH, int H, int N, int d, int M0, int Ch, const void* K,
                                    const void* V, const void* Cp, const void* Cc,
                                    int32_t* parent_idx, int32_t* code_idx, float* Vbar,
                                    int32_t* counts, void* packed, hipStream_t stream) {
-  const bool fused = Elem<T>::kBf16 && Ch >= 1 && Ch <= 8;
-  hipError_t e = d == 64 ? launch_assign<T, 64>(BH, H, N, M0, Ch, K, Cp, Cc, parent_idx, code_idx,
-                                                !fused, stream)
-                         : launch_assign<T, 128>(BH, H, N, M0, Ch, K, Cp, Cc, parent_idx,
-                                                 code_idx, !fused, stream);
-  if (e != hipSuccess) return e;
-  if (!fused) return launch_aggregate<T>(BH, N, d, M0, Ch, V, code_idx, Vbar, counts, packed, stream);
-  FusedArgs fa{K, Cp, Cc, code_idx, H};
-  if constexpr (Elem<T>::kBf16) {
-    if (d == 64)
-      return launch_aggregate_dc<T, 64, 8, true>(BH, N, M0, Ch, V, parent_idx, Vbar, counts,
-                                                 packed, fa, stream);
-    return launch_aggregate_dc<T, 128, 8, true>(BH, N, M0, Ch, V, parent_idx, Vbar, counts,
-                                                packed, fa, stream);
-  }
-  return hipErrorInvalidValue;  // not reached: fp32 takes the unfused path
+  if (d == 64)
+    return launch_assign_aggregate_d<T, 64>(BH, H, N, M0, Ch, K, V, Cp, Cc, parent_idx, code_idx,
+                                            Vbar, counts, packed, stream);
+  if (d == 128)
+    return launch_assign_aggregate_d<T, 128>(BH, H, N, M0, Ch, K, V, Cp, Cc, parent_idx, code_idx,
+                                             Vbar, counts, packed, stream);
+  return hipErrorInvalidValue;
 }
 
 template hipError_t launch_aggregate<bf16>(int, int, int, int, int, const void*, const int32_t*,

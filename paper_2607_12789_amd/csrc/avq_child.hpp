@@ -57,14 +57,10 @@ struct ChildTile {
 
 // The candidate rows of parent p of head h (A operand): lane (g, c) holds row
 // c of each tile, k-step kq at d = 32 kq + 8 g (bf16) or 4 kq + g (fp32).
-// Then each row's ||c||^2 (each lane sums its quarter of row c in order, the
-// quarters are combined in a fixed order, then moved to the lanes that hold
-// the row's products), and the rows scaled by -2.
 template <typename T, int D, int NT>
-__device__ __forceinline__ void child_rows(
+__device__ __forceinline__ void child_rows_load(
     const T* __restrict__ Cp, const T* __restrict__ Cc, int h, int M0, int Ch, int p, int g,
-    int c, typename ChildTile<T, D, NT>::Frag (&cf)[NT][ChildTile<T, D, NT>::KQ],
-    f32x4 (&cn)[NT]) {
+    int c, typename ChildTile<T, D, NT>::Frag (&cf)[NT][ChildTile<T, D, NT>::KQ]) {
   constexpr int KQ = ChildTile<T, D, NT>::KQ;
 #pragma unroll
   for (int t2 = 0; t2 < NT; ++t2) {
@@ -79,6 +75,16 @@ __device__ __forceinline__ void child_rows(
         cf[t2][kq] = row[4 * kq + g];
     }
   }
+}
+
+// Each loaded row's ||c||^2 (each lane sums its quarter of row c in order, the
+// quarters are combined in a fixed order, then moved to the lanes that hold
+// the row's products), and the rows scaled by -2.
+template <typename T, int D, int NT>
+__device__ __forceinline__ void child_rows_finish(
+    int g, typename ChildTile<T, D, NT>::Frag (&cf)[NT][ChildTile<T, D, NT>::KQ],
+    f32x4 (&cn)[NT]) {
+  constexpr int KQ = ChildTile<T, D, NT>::KQ;
 #pragma unroll
   for (int t2 = 0; t2 < NT; ++t2) {
     float part = 0.f;
@@ -91,6 +97,15 @@ __device__ __forceinline__ void child_rows(
 #pragma unroll
     for (int kq = 0; kq < KQ; ++kq) cf[t2][kq] = times_minus2(cf[t2][kq]);
   }
+}
+
+template <typename T, int D, int NT>
+__device__ __forceinline__ void child_rows(
+    const T* __restrict__ Cp, const T* __restrict__ Cc, int h, int M0, int Ch, int p, int g,
+    int c, typename ChildTile<T, D, NT>::Frag (&cf)[NT][ChildTile<T, D, NT>::KQ],
+    f32x4 (&cn)[NT]) {
+  child_rows_load<T, D, NT>(Cp, Cc, h, M0, Ch, p, g, c, cf);
+  child_rows_finish<T, D, NT>(g, cf, cn);
 }
 
 // Key fragments of one key row (B operand, column c of the tile).

@@ -1,0 +1,120 @@
+"""The aggregation's key list: heads whose keys crowd into few families.
+
+A workgroup lists the keys of its families in LDS. These cases give one
+workgroup more keys than the list holds, so that it takes its families in
+batches, and one family more than the list holds, so that the family's keys
+come in segments; families before, between and after it are small, of whole
+groups of 32 keys and one key more or less, or empty. Sums are compared with
+64-bit ones within the fp32 summation bound, counts exactly.
+"""
+import pytest
+import torch
+
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2607_12789_amd import avq
+    avq.lib()
+
+
+def crowded(M0, per_family, g):
+    """Parents of a head's keys: per_family[p] keys of parent p, shuffled."""
+    par = torch.repeat_interleave(torch.arange(M0), torch.tensor(per_family))
+    return par[torch.randperm(len(par), generator=g)]
+
+
+# keys per parent of a 16-parent head: one family of 30000 (past every list)
+# among small ones, and 16 of about 3000 (together past every list)
+GIANT = [31, 32, 33, 0, 1, 30000, 0, 64, 65, 5, 0, 0, 17, 96, 2, 0]
+BATCHES = [3000 + 37 * (p % 3) for p in range(16)]
+
+
+def reference(V, par, code, M0, Ch):
+    """64-bit sums and counts, and the sums of |v| (of one head)."""
+    Mtot = M0 * (1 + Ch)
+    n = torch.bincount(code, minlength=Mtot)
+    n[:M0] = torch.bincount(par, minlength=M0)
+    out = []
+    for v in (V.double(), V.double().abs()):
+        s = torch.zeros(Mtot, V.shape[1], dtype=torch.float64, device=V.device)
+        s.index_add_(0, par, v)
+        moved = code >= M0
+        s.index_add_(0, code[moved], v[moved])
+        out.append(s)
+    return n, out[0], out[1]
+
+
+def check(V, par, code, M0, Ch, packed, counts, Vbar):
+    n, s, mag = reference(V, par, code, M0, Ch)
+    assert torch.equal(counts.long(), n)
+    tol = torch.from_numpy(parity.gamma(n.clamp(min=1).cpu().numpy())).to(s)[:, None] * mag + 1e-30
+    assert ((Vbar.double() - s).abs() <= tol).all()
+    dt = {torch.float32: "f32", torch.bfloat16: "bf16"}[V.dtype]
+    means, n_pk, _, pad = parity.unpack_packed(packed[None, None].cpu().numpy(), M0, Ch,
+                                               V.shape[1], dt)
+    assert (pad["means"] == 0).all() and (pad["n"] == 0).all()
+    assert (n_pk[0, 0] == n.cpu().numpy()).all()
+    r_store = 2.0 ** -8 if dt == "bf16" else parity.U
+    nn = n.clamp(min=1)[:, None]
+    mean = (s / nn).cpu().numpy()
+    tol_m = (tol / nn).cpu().numpy() + (3 * parity.U + r_store) * abs(mean) + 1e-30
+    assert (abs(means[0, 0] - mean) <= tol_m).all()
+
+
+@pytest.mark.parametrize("heads", [1, 256])  # 256: all 16 families in one workgroup
+@pytest.mark.parametrize("keys", ["giant", "batches"])
+@pytest.mark.parametrize("dtype,d,Ch", [(torch.bfloat16, 128, 8), (torch.bfloat16, 64, 16),
+                                        (torch.float32, 64, 2), (torch.bfloat16, 128, 0),
+                                        (torch.float32, 128, 0)])
+def test_crowded_codes(dtype, d, Ch, keys, heads):
+    from paper_2607_12789_amd import avq
+    M0 = 16
+    g = torch.Generator().manual_seed(7)
+    par = crowded(M0, GIANT if keys == "giant" else BATCHES, g).cuda()
+    N = len(par)
+    if heads * N * d >= 2 ** 30:
+        heads = 128
+    child = torch.randint(-1, max(Ch, 1), (N,), generator=g).cuda()
+    code = torch.where(child < 0, par, M0 + par * Ch + child) if Ch else par
+    V1 = torch.randn(N, d, generator=g).to(dtype).cuda()
+    V = V1.expand(1, heads, N, d).contiguous()
+    codes = code.to(torch.int32).expand(1, heads, N).contiguous()
+    packed, counts, Vbar = avq.aggregate(V, codes, M0, Ch, sums=True)
+    for h in {0, heads // 2, heads - 1}:
+        check(V1, par, code, M0, Ch, packed[0, h], counts[0, h], Vbar[0, h])
+
+
+@pytest.mark.parametrize("keys", ["giant", "batches"])
+@pytest.mark.parametrize("dtype,d,Ch", [(torch.bfloat16, 128, 8), (torch.bfloat16, 64, 4),
+                                        (torch.bfloat16, 128, 16), (torch.float32, 64, 16),
+                                        (torch.float32, 128, 8)])
+def test_crowded_fused(dtype, d, Ch, keys):
+    """The fused pass on the same crowds: the codes of avq_assign exactly, and
+    the sums of those codes."""
+    from paper_2607_12789_amd import avq
+    M0, heads = 16, 128
+    g = torch.Generator().manual_seed(9)
+    par = crowded(M0, GIANT if keys == "giant" else BATCHES, g)
+    N = len(par)
+    Cp = torch.randn(M0, d, generator=g)
+    Cc = Cp[:, None] + 0.1 * torch.randn(M0, Ch, d, generator=g)
+    pick = torch.randint(0, Ch + 1, (N,), generator=g)
+    rows = torch.cat([Cp[:, None], Cc], 1)[par, pick]
+    K1 = (rows + 0.05 * torch.randn(N, d, generator=g)).to(dtype).cuda()
+    V1 = torch.randn(N, d, generator=g).to(dtype).cuda()
+    K, V = (x.expand(1, heads, N, d).contiguous() for x in (K1, V1))
+    cp = Cp.to(dtype).cuda().expand(heads, M0, d).contiguous()
+    cc = Cc.to(dtype).cuda().expand(heads, M0, Ch, d).contiguous()
+    p_idx, c_idx, packed, counts, Vbar = avq.assign_aggregate(K, V, cp, cc, sums=True)
+    p_ref, c_ref = avq.assign(K[:, :2].contiguous(), cp[:2].contiguous(), cc[:2].contiguous())
+    assert torch.equal(p_idx[:, :2], p_ref) and torch.equal(c_idx[:, :2], c_ref)
+    for h in {0, heads // 2, heads - 1}:
+        assert torch.equal(c_idx[0, h], c_idx[0, 0])
+        check(V1, p_idx[0, h].long(), c_idx[0, h].long(), M0, Ch, packed[0, h], counts[0, h],
+              Vbar[0, h])
