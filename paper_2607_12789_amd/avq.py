@@ -268,9 +268,7 @@ def attention_fwd(Q, Cp, Cc, packed, P: int, block_q: int, Y=None, topp_idx=None
 
 def forward(Q, K, V, Cp, Cc, P: int, block_q: int, stream=None):
     """The whole forward pass: assign, aggregate, attention. Returns Y."""
-    M0, Ch = Cc.shape[1], Cc.shape[2]
-    _, code_idx = assign(K, Cp, Cc, stream=stream)
-    packed, _, _ = aggregate(V, code_idx, M0, Ch, stream=stream)
+    _, _, packed, _, _ = assign_aggregate(K, V, Cp, Cc, stream=stream)
     return attention_fwd(Q, Cp, Cc, packed, P, block_q, stream=stream)
 
 
