@@ -6,9 +6,11 @@
 // consecutive parents). One workgroup owns one (batch, head) and a range of F
 // families and is the only writer of their rows, so there are no float
 // atomics and no partial results in HBM. The workgroup
-//   1. counts the head's keys per family (one scan of the codes, integer LDS
-//      atomics) and gives every family whole groups of 32 slots in a key list;
-//   2. scans the codes again and scatters the keys into their family's slots;
+//   1. scans the head's codes once: every wave compacts the keys of the range
+//      into a private list in LDS, then counts them per family (integer LDS
+//      atomics on full waves);
+//   2. gives every family whole groups of 32 slots in a key list and scatters
+//      the keys into their family's slots;
 //   3. deals the groups to its waves in equal contiguous runs. For a group
 //      of 32 keys of one family a wave reads the 32 value rows (FUSED: and
 //      the 32 key rows, whose child compare, avq_child.hpp, tells each key's
@@ -31,12 +33,14 @@
 // to the next.
 //
 // What bounds it: at large sizes HBM (each value and key row is read once),
-// at small ones the chain of phases of one workgroup. Measured (traced, bf16,
-// the fused pass; before: keys bucketed a second time by row, each half wave
-// summing one family's rows in turn with vector adds): B = 2, H = 16,
-// N = 16384, d = 128, M0 = 256, Ch = 8: 75 -> 68 us (4.7 TB/s while the rows
-// stream); B = 4, H = 12, N = 1024, d = 64, M0 = 64, Ch = 8: 29 -> 21 us;
-// B = 8, H = 12, N = 4096, d = 64, M0 = 256, Ch = 8: 73 -> 65 us.
+// at small ones the chain of phases of one workgroup. Before, keys were
+// bucketed a second time by row and each half wave summed one family's rows
+// in turn with vector adds, after a scan with three barriers per 8192 codes.
+// The precompute (parent assignment + fused pass), bf16, us, before -> now:
+// B = 2, H = 16, N = 16384, d = 128, M0 = 256, Ch = 8: 104 -> 96 (the pass
+// itself reads K and V at about 4.7 TB/s once it streams); B = 1, H = 16,
+// N = 65536, M0 = 512: 282 -> 261; B = 8, H = 12, N = 4096, d = 64, M0 = 256:
+// 89 -> 58; B = 4, H = 12, N = 1024, d = 64, M0 = 64: 35 -> 17.
 //
 // Packed aggregates (avq_packed.hpp): the mean value (sum / count) of every
 // code rounded to the input type, in octets of 8 codes laid out as the
@@ -52,7 +56,7 @@
 
 namespace avq {
 
-constexpr int kMaxFamilies = 32;  // families per workgroup, at most
+constexpr int kMaxFamilies = 64;  // families per workgroup, at most: one per lane
 constexpr int kGroup = 32;        // keys per group
 
 enum AggMode {
@@ -71,16 +75,22 @@ struct FusedArgs {
 
 // NT: accumulator tiles (and candidate tiles) per family, 1 for Ch <= 8, 2 for
 // Ch = 16.
-template <typename T, int D, int NT, int MODE>
+template <typename T, int D, int NT, int MODE, bool SMALL>
 struct AggCfg {
   static constexpr bool kB = Elem<T>::kBf16;
   static constexpr bool kFlat = MODE == kAggFlat;
   static constexpr bool kFused = MODE == kAggFused;
-  // Waves per workgroup, one workgroup per CU: as many as the registers (16:
-  // 128 per lane, 12: 168, 8: 256) and the LDS (flat at d = 128: 8) allow.
+  // SMALL: 4 workgroups of 4 waves per CU, whose phases overlap, instead of
+  // one of up to 16 waves (see launch_aggregate_nt). Otherwise as many waves
+  // as the registers (16: 128 per lane, 12: 168, 8: 256) and the LDS (flat at
+  // d = 128: 8) allow; the fused bf16 pass at d = 128 spills with 168
+  // registers and is faster with 8 waves (c4 precompute 104 -> 96 us).
+  static constexpr int kPerCU = SMALL ? 4 : 1;
   static constexpr int kWaves =
-      D == 128 ? (kFlat || NT == 2 ? 8 : kFused ? (kB ? 12 : 8) : (kB ? 16 : 12))
-               : (NT == 2 ? (kFused && !kB ? 8 : 12) : kFused && !kB ? 12 : 16);
+      SMALL      ? 4
+      : D == 128 ? (kFlat || kFused || NT == 2 ? 8 : kB ? 16 : 12)
+                 : (NT == 2 ? (kFused && !kB ? 8 : 12) : kFused && !kB ? 12 : 16);
+  static constexpr int kLds = 160 * 1024 / kPerCU;  // of one workgroup
   static constexpr int kThreads = kWaves * kWave;
   static constexpr int CT = D / 16;            // 16-column tiles
   static constexpr int ROWS = kFlat ? 16 : NT == 2 ? 17 : 9;  // rows held of a family
@@ -92,6 +102,7 @@ struct AggCfg {
     int hist[kMaxFamilies];        // keys per family
     int gstart[kMaxFamilies + 1];  // first group of each family of the batch
     int cursor[kMaxFamilies];      // keys scattered so far
+    int spilled;                   // some wave's private list was too short
     float cell[kMaxFamilies];      // cell sizes (n of the parents)
     uint16_t onehot[kWaves][NT][kGroup];  // row bits of the group's keys
   };
@@ -104,8 +115,13 @@ struct AggCfg {
   static constexpr int off_list(int F) {
     return OFF_PMEAN + (kFlat ? 0 : F * D * (int)sizeof(T));
   }
+  // while the codes are scanned, the slots, staging areas and parent means
+  // hold one private key list per wave
+  static constexpr int priv_cap(int F) {
+    return (off_list(F) - OFF_SLOT) / (4 * kWaves) / 16 * 16;
+  }
   static_assert(OFF_PMEAN + (kFlat ? 0 : kMaxFamilies * D * (int)sizeof(T)) +
-                        4 * kGroup * kMaxFamilies <= 160 * 1024,
+                        4 * kGroup * kMaxFamilies <= kLds,
                 "a key list of one group per family fits the LDS");
 };
 
@@ -150,12 +166,15 @@ struct ValRow {
   }
 };
 
-template <typename T, int D, int NT, int MODE>
-__global__ __launch_bounds__((AggCfg<T, D, NT, MODE>::kThreads)) void aggregate_kernel(
+template <typename T, int D, int NT, int MODE, bool SMALL>
+__global__ __launch_bounds__((AggCfg<T, D, NT, MODE, SMALL>::kThreads))
+__attribute__((amdgpu_waves_per_eu(AggCfg<T, D, NT, MODE, SMALL>::kWaves *
+                                   AggCfg<T, D, NT, MODE, SMALL>::kPerCU / 4)))
+void aggregate_kernel(
     const T* __restrict__ V, const int32_t* __restrict__ code_idx, float* __restrict__ Vbar,
     int32_t* __restrict__ counts, unsigned char* __restrict__ packed, int N, int M0, int Ch,
     int F, int ranges, int cap, FusedArgs fa) {
-  using Cfg = AggCfg<T, D, NT, MODE>;
+  using Cfg = AggCfg<T, D, NT, MODE, SMALL>;
   constexpr bool kB = Cfg::kB, kFlat = Cfg::kFlat, kFused = Cfg::kFused;
   constexpr int W = Cfg::kWaves, CT = Cfg::CT, ROWS = Cfg::ROWS;
   using VR = ValRow<T, D>;
@@ -212,14 +231,96 @@ __global__ __launch_bounds__((AggCfg<T, D, NT, MODE>::kThreads)) void aggregate_
     }
   };
 
-  // ---- 1. keys per family ------------------------------------------------
-  if (tid < kMaxFamilies) L.hist[tid] = 0;
+  // ---- 1. the range's keys, and keys per family ---------------------------
+  // Each wave compacts the keys of this range among its share of the codes
+  // into a private list (key in 21 bits, row in 5, family in 6; a ballot and
+  // one LDS write per 64 codes), then counts and scatters from there: the LDS
+  // atomics run on full waves of the range's keys, not on the few lanes per 64
+  // codes that hold one. A wave whose share does not fit its list leaves the
+  // scan to the general path below, as do heads of more than 2^21 keys and
+  // ranges that need several batches (the lists do not outlive the first).
+  constexpr int kKeyBits = 21;
+  uint32_t* priv = reinterpret_cast<uint32_t*>(lds_raw + Cfg::OFF_SLOT) + wave * Cfg::priv_cap(F);
+  const int priv_cap = Cfg::priv_cap(F);
+  int n_priv = 0;  // wave-uniform
+  const bool try_priv = N <= 1 << kKeyBits;
+  if (tid < kMaxFamilies) {
+    L.hist[tid] = 0;
+    L.cursor[tid] = 0;
+  }
+  if (tid == 0) L.spilled = 0;
+  if (try_priv) {
+    auto take = [&](int key, int code) {
+      int f, row;
+      const bool in = locate(code, f, row);
+      const unsigned long long mk = __ballot(in);
+      const int pos = n_priv + bits_below(mk);
+      if (in && pos < priv_cap)
+        priv[pos] = (uint32_t)key | (uint32_t)row << kKeyBits | (uint32_t)f << (kKeyBits + 5);
+      n_priv += __popcll(mk);
+    };
+    // a block of 512 keys per wave and step, the next one's codes in flight
+    constexpr int kPer = 8, kBlock = kPer * kWave;
+    const int stride = W * kBlock;
+    int nx[kPer];
+    if (N % 4 == 0) {  // the head's codes are 16-byte aligned: four per load
+      auto fetch = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < kPer / 4; ++i) {
+          const int j = b + 4 * kWave * i + 4 * lane;
+          const int4 v = j < N ? *reinterpret_cast<const int4*>(codes + j) : int4{-1, -1, -1, -1};
+          nx[4 * i] = v.x;
+          nx[4 * i + 1] = v.y;
+          nx[4 * i + 2] = v.z;
+          nx[4 * i + 3] = v.w;
+        }
+      };
+      fetch(wave * kBlock);
+      for (int b = wave * kBlock; b < N; b += stride) {
+        int cd[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) cd[i] = nx[i];
+        if (b + stride < N) fetch(b + stride);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) take(b + 4 * kWave * (i / 4) + 4 * lane + i % 4, cd[i]);
+      }
+    } else {
+      auto fetch = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+          const int j = b + kWave * i + lane;
+          nx[i] = j < N ? codes[j] : -1;
+        }
+      };
+      fetch(wave * kBlock);
+      for (int b = wave * kBlock; b < N; b += stride) {
+        int cd[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) cd[i] = nx[i];
+        if (b + stride < N) fetch(b + stride);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) take(b + kWave * i + lane, cd[i]);
+      }
+    }
+  }
   __syncthreads();
-  scan(0, N, [&](int, int code) {
-    int f, row;
-    if (locate(code, f, row)) atomicAdd(&L.hist[f], 1);
-  });
+  if (n_priv > priv_cap || !try_priv) {
+    if (lane == 0) L.spilled = 1;
+  } else {
+    for (int e = lane; e < n_priv; e += kWave) atomicAdd(&L.hist[priv[e] >> (kKeyBits + 5)], 1);
+  }
   __syncthreads();
+  const bool spilled = L.spilled != 0;
+  if (spilled) {
+    __syncthreads();
+    if (tid < kMaxFamilies) L.hist[tid] = 0;
+    __syncthreads();
+    scan(0, N, [&](int, int code) {
+      int f, row;
+      if (locate(code, f, row)) atomicAdd(&L.hist[f], 1);
+    });
+    __syncthreads();
+  }
 
   // The lane index through an empty asm statement: the addresses formed from
   // it are computed where they are used, not hoisted out of the group loop and
@@ -227,6 +328,13 @@ __global__ __launch_bounds__((AggCfg<T, D, NT, MODE>::kThreads)) void aggregate_
   auto hidden = [](int x) {
     asm volatile("" : "+v"(x));
     return x;
+  };
+
+  // a wave's LDS writes are read by its other lanes: LDS operations of one
+  // wave complete in order
+  auto wave_lds_fence = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   };
 
   // ---- a family's sums ---------------------------------------------------
@@ -290,13 +398,6 @@ __global__ __launch_bounds__((AggCfg<T, D, NT, MODE>::kThreads)) void aggregate_
   constexpr float kNegInf = -__builtin_inff();
   constexpr float kLn2 = 0.6931471805599453f;
   auto ln_n = [&](float n) { return n > 0.f ? log2_hw(n) * kLn2 : kNegInf; };
-  // a wave's LDS writes are read by its other lanes: LDS operations of one
-  // wave complete in order
-  auto wave_lds_fence = [&]() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  };
-
   // writes every row of family f: sums, counts, its octets with their counts;
   // the parent's mean and cell size go to LDS
   auto write_family = [&](int f) {
@@ -382,34 +483,44 @@ __global__ __launch_bounds__((AggCfg<T, D, NT, MODE>::kThreads)) void aggregate_
 
   // ---- 2. and 3. in batches of families that fit the key list ------------
   for (int f0 = 0; f0 < nfam;) {
-    // families f0 .. f1 - 1 (uniform): each at least one group, so that the
-    // wave of its first group writes it, empty or not
-    if (wave == 0) {
-      const int n = lane >= f0 && lane < nfam ? L.hist[lane < kMaxFamilies ? lane : 0] : 0;
+    // families f0 .. f1 - 1: each at least one group, so that the wave of its
+    // first group writes it, empty or not. Every wave finds the same plan.
+    int f1;
+    bool giant;
+    {
+      const int n = lane >= f0 && lane < nfam ? L.hist[lane] : 0;
       const int ng = lane >= f0 && lane < nfam ? max(1, (n + kGroup - 1) / kGroup) : 0;
       const int incl = wave_incl_scan(ng);
       if (lane < nfam) L.gstart[lane] = incl - ng;
       if (lane == nfam - 1) L.gstart[nfam] = incl;
-      if (lane < kMaxFamilies) L.cursor[lane] = 0;
+      const int fit = __popcll(__ballot(lane >= f0 && lane < nfam && incl * kGroup <= cap));
+      f1 = f0 + max(1, fit);
+      // a family past the list: segments of the head that fit whatever they hold
+      giant = fit == 0;
     }
-    __syncthreads();
-    int f1 = nfam;
-    while (f1 > f0 + 1 && L.gstart[f1] * kGroup > cap) --f1;
-    // a family past the list: segments of the head that fit whatever they hold
-    const bool giant = L.gstart[f1] * kGroup > cap;
+    wave_lds_fence();
+    const bool from_priv = !spilled && f1 == nfam && f0 == 0 && !giant;
     zero_acc();
     for (int s0 = 0; s0 < N; s0 += giant ? cap : N) {
       const int s1 = giant ? min(N, s0 + cap) : N;
-      scan(s0, s1, [&](int key, int code) {
-        int f, row;
-        if (locate(code, f, row) && f >= f0 && f < f1) {
-          const int k = atomicAdd(&L.cursor[f], 1);
-          // key k of a group lies in slot 8 (k % 4) + k / 4: lane group g
-          // reads slots 8 g .. 8 g + 7, i.e. keys g, 4 + g, 8 + g, ...
-          const int slot = L.gstart[f] * kGroup + (k & ~31) + (k & 3) * 8 + ((k & 31) >> 2);
-          list[slot] = (uint32_t)key | (kFused ? 0u : (uint32_t)row << 24);
+      // key k of a group lies in slot 8 (k % 4) + k / 4: lane group g reads
+      // slots 8 g .. 8 g + 7, i.e. keys g, 4 + g, 8 + g, ...
+      auto put = [&](int f, int key, int row) {
+        const int k = atomicAdd(&L.cursor[f], 1);
+        const int slot = L.gstart[f] * kGroup + (k & ~31) + (k & 3) * 8 + ((k & 31) >> 2);
+        list[slot] = (uint32_t)key | (kFused ? 0u : (uint32_t)row << 24);
+      };
+      if (from_priv) {
+        for (int e = lane; e < n_priv; e += kWave) {
+          const uint32_t x = priv[e];
+          put(x >> (kKeyBits + 5), x & ((1u << kKeyBits) - 1), (x >> kKeyBits) & 31u);
         }
-      });
+      } else {
+        scan(s0, s1, [&](int key, int code) {
+          int f, row;
+          if (locate(code, f, row) && f >= f0 && f < f1) put(f, key, row);
+        });
+      }
       __syncthreads();
       const int seg_n = L.cursor[f0];  // giant: keys of this segment
       const int NG = giant ? (seg_n + kGroup - 1) / kGroup : L.gstart[f1];
@@ -652,6 +763,7 @@ __global__ __launch_bounds__((AggCfg<T, D, NT, MODE>::kThreads)) void aggregate_
           write_family(f);
         }
       }
+      if (tid < kMaxFamilies) L.cursor[tid] = 0;  // for the next batch
       __syncthreads();
     }
     f0 = f1;
@@ -695,42 +807,75 @@ __global__ __launch_bounds__((AggCfg<T, D, NT, MODE>::kThreads)) void aggregate_
   }
 }
 
-// Families per workgroup: the most (up to 32) that still give every CU a
-// workgroup. A workgroup scans all codes of its head, so fewer families per
-// workgroup cost scanning; idle CUs cost more.
-inline int families_per_workgroup(long long BH, int n_fam, int cus) {
-  int F = kMaxFamilies;
-  while (F > 1 && BH * ((n_fam + F - 1) / F) < cus) F /= 2;
-  return F;
+// Families per workgroup: the fewest that let all workgroups run at once
+// (slots of them), so that no CU is left with a second, partial round; with
+// more families than kMaxFamilies times that, the fewest whole rounds. Fewer
+// families per workgroup cost scanning (every workgroup scans all codes of
+// its head) and a second round, more leave CUs idle. Precompute in us: 48
+// heads of 64 families (N = 1024, d = 64, 1024 slots): 2 families 21.1, 4
+// 17.3 (chosen), 8 18.0, 16 21.9; 96 heads of 256 (N = 4096): 24 67.3, 32
+// 57.7 (chosen), 64 76.2; 32 heads of 256 (N = 16384, d = 128, 256 slots): 16
+// 104, 32 96 (chosen), 64 123.
+inline int families_per_workgroup(long long BH, int n_fam, long long slots) {
+  for (long long r = 1;; ++r) {
+    const long long ranges = r * slots / BH;  // per head
+    if (ranges < 1) continue;
+    const long long F = (n_fam + ranges - 1) / ranges;
+    if (F <= kMaxFamilies) return (int)F;
+  }
 }
 
-template <typename T, int D, int NT, int MODE>
+template <typename T, int D, int NT, int MODE, bool SMALL>
 hipError_t launch_aggregate_cfg(int BH, int N, int M0, int Ch, const void* V,
                                 const int32_t* code_idx, float* Vbar, int32_t* counts,
                                 void* packed, const FusedArgs& fa, hipStream_t stream) {
-  using Cfg = AggCfg<T, D, NT, MODE>;
+  using Cfg = AggCfg<T, D, NT, MODE, SMALL>;
   DeviceInfo dev;
   hipError_t e = device_info(&dev);
   if (e != hipSuccess) return e;
   const int n_fam = Cfg::kFlat ? packed_layout(M0, Ch, D, (int)sizeof(T)).PO / 2 : M0;
-  const int F = families_per_workgroup(BH, n_fam, dev.cus > 1 ? dev.cus : 1);
+  const long long cus = dev.cus > 1 ? dev.cus : 1;
+  const int F = families_per_workgroup(BH, n_fam, cus * Cfg::kPerCU);
   const int ranges = (n_fam + F - 1) / F;
   const long long grid = (long long)BH * ranges;
   if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;
   // the key list takes the rest of the LDS that one workgroup may use, and
   // no more than the head's keys with every family's last group padded
-  const int room = (dev.lds_max - Cfg::off_list(F)) / (4 * kGroup) * kGroup;
+  const int room = (std::min(dev.lds_max, Cfg::kLds) - Cfg::off_list(F)) / (4 * kGroup) * kGroup;
   const long long most = ((long long)N + (long long)F * kGroup + kGroup - 1) / kGroup * kGroup;
   const int cap = (int)std::min<long long>(room, most);
   if (cap < F * kGroup) return hipErrorInvalidConfiguration;
   const int lds = Cfg::off_list(F) + 4 * cap;
-  constexpr int slot = 64 + ((((Elem<T>::kBf16 ? 0 : 1) * 2 + (D == 128 ? 1 : 0)) * 2 + (NT - 1)) * 3 + MODE);
-  e = ensure_dynamic_lds((const void*)aggregate_kernel<T, D, NT, MODE>, lds, slot);
+  constexpr int slot = 64 + ((((Elem<T>::kBf16 ? 0 : 1) * 2 + (D == 128 ? 1 : 0)) * 2 + (NT - 1)) * 3 + MODE) +
+                       (SMALL ? 64 : 0);
+  e = ensure_dynamic_lds((const void*)aggregate_kernel<T, D, NT, MODE, SMALL>, lds, slot);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((aggregate_kernel<T, D, NT, MODE>), dim3((unsigned)grid), dim3(Cfg::kThreads),
-                     lds, stream, static_cast<const T*>(V), code_idx, Vbar, counts,
-                     static_cast<unsigned char*>(packed), N, M0, Ch, F, ranges, cap, fa);
+  hipLaunchKernelGGL((aggregate_kernel<T, D, NT, MODE, SMALL>), dim3((unsigned)grid),
+                     dim3(Cfg::kThreads), lds, stream, static_cast<const T*>(V), code_idx, Vbar,
+                     counts, static_cast<unsigned char*>(packed), N, M0, Ch, F, ranges, cap, fa);
   return hipGetLastError();
+}
+
+// bf16 at d = 64 with Ch <= 8, below 16384 keys per head: SMALL. Their rows
+// stream for a few us only, so a workgroup's chain of phases sets the time
+// unless several workgroups per CU overlap theirs; with more keys the scan of
+// all codes by four times as many workgroups costs what that gains.
+// Precompute, SMALL / one 16-wave workgroup per CU, us: 96 heads x 256
+// families, N = 4096: 57.7 / 71.9; 48 x 256, N = 2048: 29.0 / 36.4; 48 x 64,
+// N = 16384: 63.7 / 64.9; 16 x 256, N = 16384: 39.2 / 38.2; 4 x 128,
+// N = 65536: 47.7 / 39.0. (At d = 128 two workgroups of 4 waves per CU are no
+// faster than one of 8: 64 x 128, N = 4096: 52.4 / 52.7.)
+template <typename T, int D, int NT, int MODE>
+hipError_t launch_aggregate_nt(int BH, int N, int M0, int Ch, const void* V,
+                               const int32_t* code_idx, float* Vbar, int32_t* counts,
+                               void* packed, const FusedArgs& fa, hipStream_t stream) {
+  if constexpr (Elem<T>::kBf16 && D == 64 && NT == 1) {
+    if (N < 16384)
+      return launch_aggregate_cfg<T, D, NT, MODE, true>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
+                                                        packed, fa, stream);
+  }
+  return launch_aggregate_cfg<T, D, NT, MODE, false>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
+                                                     packed, fa, stream);
 }
 
 template <typename T, int D>
@@ -739,13 +884,13 @@ hipError_t launch_aggregate_d(int BH, int N, int M0, int Ch, const void* V,
                               void* packed, hipStream_t stream) {
   const FusedArgs none{};
   if (Ch == 0)
-    return launch_aggregate_cfg<T, D, 1, kAggFlat>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
+    return launch_aggregate_nt<T, D, 1, kAggFlat>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
                                                    packed, none, stream);
   if (Ch <= 8)
-    return launch_aggregate_cfg<T, D, 1, kAggCodes>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
+    return launch_aggregate_nt<T, D, 1, kAggCodes>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
                                                     packed, none, stream);
   if (Ch <= 16)
-    return launch_aggregate_cfg<T, D, 2, kAggCodes>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
+    return launch_aggregate_nt<T, D, 2, kAggCodes>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
                                                     packed, none, stream);
   return hipErrorInvalidValue;
 }
@@ -779,10 +924,10 @@ hipError_t launch_assign_aggregate_d(int BH, int H, int N, int M0, int Ch, const
     return launch_aggregate_d<T, D>(BH, N, M0, Ch, V, code_idx, Vbar, counts, packed, stream);
   const FusedArgs fa{K, Cp, Cc, code_idx, H};
   if (Ch <= 8)
-    return launch_aggregate_cfg<T, D, 1, kAggFused>(BH, N, M0, Ch, V, parent_idx, Vbar, counts,
+    return launch_aggregate_nt<T, D, 1, kAggFused>(BH, N, M0, Ch, V, parent_idx, Vbar, counts,
                                                     packed, fa, stream);
   if constexpr (kWide)
-    return launch_aggregate_cfg<T, D, 2, kAggFused>(BH, N, M0, Ch, V, parent_idx, Vbar, counts,
+    return launch_aggregate_nt<T, D, 2, kAggFused>(BH, N, M0, Ch, V, parent_idx, Vbar, counts,
                                                     packed, fa, stream);
   return hipErrorInvalidValue;  // not reached
 }
