@@ -1,7 +1,8 @@
 // Fused refined-codebook attention (Sec. 4.3, Alg. 2) for gfx950.
 //
 // One workgroup processes one query tile (block_q consecutive tokens of one
-// (batch, head)); each wave owns 32 query rows. Everything is computed
+// (batch, head)), or two tiles of at most 64 queries; each wave owns 32 query
+// rows. Everything is computed
 // transposed, codewords x queries: S^T = C . Q^T and Xbar^T = Vmean^T . W^T,
 // with 16x16x32 bf16 (16x16x4 fp32) MFMA. A lane owns one query column and,
 // in a pair of 16-row logit tiles, 8 consecutive codes (one octet of the
@@ -63,14 +64,17 @@
 // With a query order, tile position i takes token order[i]: Q rows are read
 // from, and Y rows written to, those tokens.
 #include "avq_common.hpp"
+#include "avq_launch.hpp"
 #include "avq_packed.hpp"
 
 #include <type_traits>
 
 namespace avq {
 
-template <typename T, int D, int MAXW>
+// TPW: query tiles per workgroup, each with MAXW / TPW waves
+template <typename T, int D, int MAXW, int TPW>
 struct AttnCfg {
+  static constexpr int WPT = MAXW / TPW;          // waves per tile
   static constexpr bool kB = Elem<T>::kBf16;
   static constexpr int RPW = 32;                  // query rows per wave (16 QS)
   static constexpr int QS = RPW / 16;             // query subtiles per wave
@@ -95,10 +99,10 @@ struct AttnCfg {
   static constexpr int NBUF = 2 * BUF_BYTES <= 72 * 1024 ? 2 : 1;
   // after the buffers
   static constexpr size_t OFF_LW = (size_t)NBUF * BUF_BYTES;    // [2][MAXW][CW] f32
-  static constexpr size_t OFF_WF = OFF_LW + 2 * MAXW * CW * 4;  // [M0MAX] f32
-  static constexpr size_t OFF_SEL = OFF_WF + M0MAX * 4;         // [M0MAX] i32
-  static constexpr size_t LDS_BYTES = OFF_SEL + M0MAX * 4;
-  static constexpr int kWavesPerEu = (kB && D == 64) ? 3 : 2;
+  static constexpr size_t OFF_WF = OFF_LW + 2 * MAXW * CW * 4;  // [TPW][M0MAX] f32
+  static constexpr size_t OFF_SEL = OFF_WF + TPW * M0MAX * 4;   // [TPW][M0MAX] i32
+  static constexpr size_t LDS_BYTES = OFF_SEL + TPW * M0MAX * 4;
+  static constexpr int kWavesPerEu = (kB && D == 64) ? 3 : 2;  // 4-wave workgroups per CU
   static_assert(COPIES % MAXW == 0 || COPIES < MAXW, "copies split evenly over the waves");
   static_assert(OCPY >= 1 && (OCPY & (OCPY - 1)) == 0, "whole wave copies per octet");
 };
@@ -134,11 +138,11 @@ __device__ __forceinline__ int row_swizzle(int r) {
 // each), so that other tiles' MFMA work runs while one workgroup waits.
 // TILED: importance with the count-extrapolated denominator of App. B, one
 // codeword tile per chunk, computed in the parent sweep (no second sweep).
-template <typename T, int D, int MAXW, bool TILED>
+template <typename T, int D, int MAXW, int TPW, bool TILED>
 __global__ __launch_bounds__(MAXW * 64)
-__attribute__((amdgpu_waves_per_eu(AttnCfg<T, D, MAXW>::kWavesPerEu)))
+__attribute__((amdgpu_waves_per_eu(AttnCfg<T, D, MAXW, TPW>::kWavesPerEu)))
 void attention_kernel(AttnArgs args) {
-  using Cfg = AttnCfg<T, D, MAXW>;
+  using Cfg = AttnCfg<T, D, MAXW, TPW>;
   constexpr bool kB = Cfg::kB;
   constexpr int QS = Cfg::QS, CW = Cfg::CW, TPC = Cfg::TPC, KQ = Cfg::KQ, DT = Cfg::DT,
                 U = Cfg::U, EPU = Cfg::EPU, CPW = Cfg::CPW,
@@ -150,8 +154,9 @@ void attention_kernel(AttnArgs args) {
 
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   float* lw = reinterpret_cast<float*>(lds_raw + Cfg::OFF_LW);   // per-wave importance
-  float* lwf = reinterpret_cast<float*>(lds_raw + Cfg::OFF_WF);  // importance
-  int* lsel = reinterpret_cast<int*>(lds_raw + Cfg::OFF_SEL);    // selected, index order
+  // importance and selected parents (index order) of each tile
+  float* lwf_all = reinterpret_cast<float*>(lds_raw + Cfg::OFF_WF);
+  int* lsel_all = reinterpret_cast<int*>(lds_raw + Cfg::OFF_SEL);
 
   const T* __restrict__ Q = static_cast<const T*>(args.Q);
   const T* __restrict__ Cp = static_cast<const T*>(args.Cp);
@@ -164,13 +169,23 @@ void attention_kernel(AttnArgs args) {
   const int wave = tid / kWave, lane = tid % kWave;
   const int g = lane / 16, c = lane % 16;
   const int tile = xcd_remap(blockIdx.x, gridDim.x);
-  const int bh = tile / args.n_tiles, t = tile % args.n_tiles;
+  // a workgroup's TPW tiles belong to one (batch, head); past the last tile
+  // its waves have no rows and only copy
+  const int groups = (args.n_tiles + TPW - 1) / TPW;
+  const int bh = tile / groups, t0 = tile % groups * TPW;
   const int h = bh % args.H;
+  const int sub = wave / Cfg::WPT;  // the wave's tile in the workgroup
+  const int t = t0 + sub;
   const int q_begin = t * args.block_q;
   const int q_end = min(q_begin + args.block_q, N);
-  const int row0 = q_begin + wave * Cfg::RPW;
-  const bool has_rows = row0 < q_end;                                 // wave-uniform
-  const int n_active = (q_end - q_begin + Cfg::RPW - 1) / Cfg::RPW;  // waves with rows
+  const int row0 = q_begin + wave % Cfg::WPT * Cfg::RPW;
+  const bool has_rows = t < args.n_tiles && row0 < q_end;  // wave-uniform
+  // waves of tile i with rows
+  auto active = [&](int i) {
+    const int rows = min(args.block_q, N - (t0 + i) * args.block_q);
+    return max(0, (rows + Cfg::RPW - 1) / Cfg::RPW);
+  };
+  const int* lsel = lsel_all + sub * Cfg::M0MAX;
   const unsigned char* pk = args.packed + (size_t)bh * PL.bytes;
   const T* cp_head = Cp + (size_t)h * M0 * D;
   const T* cc_head = Cc + (size_t)h * M0 * Ch * D;
@@ -269,25 +284,29 @@ void attention_kernel(AttnArgs args) {
     if (cwave == MAXW - 1 && lane < 32)  // 8 octets x 64 bytes of count info
       copy(r_pk, moff, info_off + (uint32_t)(8 * k) * 64u, B + Cfg::OFF_I);
   };
-  // child chunk k: octet o (o = 8k + os) belongs to selected parent o >> co_shift
-  // (CO is 1 or 2); octets past the last read the empty octet (means and
-  // counts) and the last octet's rows, rows past Ch - 1 the last child.
-  // With Ch <= 4 the copies that hold only rows 4..7 of their octets
-  // (padding, never read) are not made.
+  // child chunk k: octet slot os of the chunk holds octet o = OPT k + os % OPT
+  // of tile os / OPT (OPT octets per tile: with two tiles, one tile pair
+  // each). Octet o belongs to selected parent o >> co_shift (CO is 1 or 2);
+  // octets past the last read the empty octet (means and counts) and the last
+  // octet's rows, rows past Ch - 1 the last child. With Ch <= 4 and one tile
+  // the copies that hold only rows 4..7 of their octets (padding, never read)
+  // are not made.
+  constexpr int OPT = 8 / TPW;
   const int n_child_oct = Ch > 1 ? P * CO : 0;
   const int co_shift = CO == 2 ? 1 : 0;
-  const bool half_child = Ch <= 4;  // rows 4..7 of every child octet are padding
+  const bool half_child = TPW == 1 && Ch <= 4;  // rows 4..7 of every child octet are padding
   auto issue_child = [&](int k, int b) {
     const uint32_t B = (uint32_t)(b * Cfg::BUF_BYTES);
-    // lane l holds the selected parent of octet 8k + (l mod 8) (clamped to the
-    // last octet); a copy takes the one of its octet with a lane read
-    const int sel_l = lsel[min(8 * k + (lane & 7), n_child_oct - 1) >> co_shift];
+    // lane l holds the selected parent of octet slot l mod 8 (clamped to the
+    // last octet); a copy takes the one of its slot with a lane read
+    const int sel_l = lsel_all[(lane & 7) / OPT * Cfg::M0MAX +
+                               (min(OPT * k + (lane & (OPT - 1)), n_child_oct - 1) >> co_shift)];
     if (Ch >= 8) {  // every row of a copy is a child
 #pragma unroll
       for (int i = 0; i < CPW; ++i) {
         const int j = cwave + MAXW * i;
         const int os = (RPC * j) / 8;
-        const int o = min(8 * k + os, n_child_oct - 1);
+        const int o = min(OPT * k + os % OPT, n_child_oct - 1);
         const int jj = o - ((o >> co_shift) << co_shift);  // child octet of the parent
         const int par = __builtin_amdgcn_readlane(sel_l, os);
         const int u = jj * 8 + (RPC * j) % 8;  // the copy's first row among the children
@@ -299,7 +318,7 @@ void attention_kernel(AttnArgs args) {
         const int j = cwave + MAXW * i;
         if (RPC <= 4 && half_child && (RPC * j) % 8 >= 4) continue;
         const int os = (RPC * j) / 8;
-        const int o = min(8 * k + os, n_child_oct - 1);
+        const int o = min(OPT * k + os % OPT, n_child_oct - 1);
         const int jj = o - ((o >> co_shift) << co_shift);
         const int par = __builtin_amdgcn_readlane(sel_l, os);
         const int u = jj * 8 + (RPC * j) % 8;
@@ -311,15 +330,17 @@ void attention_kernel(AttnArgs args) {
     for (int i = 0; i < CPW; ++i) {
       const int j = cwave + MAXW * i;
       const int os = j / OCPY;
-      const int o = 8 * k + os;
+      const int o = OPT * k + os % OPT;
       const int par = __builtin_amdgcn_readlane(sel_l, os);
       const int oct = o >= n_child_oct ? ZO : PO + (par << co_shift) + (o - ((o >> co_shift) << co_shift));
       copy(r_pk, moff, (uint32_t)oct * OctB + (uint32_t)(j % OCPY) * 1024u, B + Cfg::OFF_V + 1024 * j);
     }
-    if (cwave == MAXW - 1 && lane < 32) {  // count info: lane's octet lane / 4
-      const int o = 8 * k + lane / 4;
+    if (cwave == MAXW - 1 && lane < 32) {  // count info: lane's octet slot lane / 4
+      const int os = lane / 4, o = OPT * k + os % OPT;
       const int sl = o >> co_shift;
-      const int oct = o >= n_child_oct ? ZO : PO + (lsel[sl] << co_shift) + (o - (sl << co_shift));
+      const int oct = o >= n_child_oct ? ZO
+                                       : PO + (lsel_all[os / OPT * Cfg::M0MAX + sl] << co_shift) +
+                                             (o - (sl << co_shift));
       copy(r_pk, (uint32_t)oct * 64u + (uint32_t)(16 * (lane % 4)), info_off, B + Cfg::OFF_I);
     }
   };
@@ -737,6 +758,22 @@ void attention_kernel(AttnArgs args) {
     }
   };
 
+  // One tile pair of a child chunk (two tiles per workgroup: pair b is the
+  // wave's tile's)
+  auto child_pair = [&](const unsigned char* B, int b) {
+    f32x4 S[2][QS];
+    float rs[2][QS];
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    logits(B, 2 * b, S[0], zero, false);
+    logits(B, 2 * b + 1, S[1], zero, false);
+    const ValOps v = load_vals(B, b);
+    child_recover(S, rs);
+    child_bias(B, b, S);
+    check_chunk(S, S);
+    child_weights(B, b, S, rs);
+    mfma_vals(B, b, v, S);
+  };
+
   const bool need_importance =
       (P > 0 && P < M0) || args.importance != nullptr || (P > 0 && args.topp_idx != nullptr);
   const int n_pchunks = PO / 8;
@@ -820,13 +857,17 @@ void attention_kernel(AttnArgs args) {
   };
   // sum the wave partials of chunk k (slot k % 2) in a fixed order
   auto importance_flush = [&](int k) {
-    if (tid < CW) {
-      const int a = CW * k + tid;
+    if (tid < TPW * CW) {
+      const int i = tid / CW, x = tid % CW;  // tile, code of the chunk
+      const int a = CW * k + x;
+      const int n_active = active(i);
       float acc = 0.f;
-      for (int wv = 0; wv < n_active; ++wv) acc += lw[((k % 2) * MAXW + wv) * CW + tid];
+      for (int wv = 0; wv < n_active; ++wv)
+        acc += lw[((k % 2) * MAXW + i * Cfg::WPT + wv) * CW + x];
       if (a < M0) {
-        lwf[a] = acc;
-        if (args.importance) args.importance[((size_t)bh * args.n_tiles + t) * M0 + a] = acc;
+        lwf_all[i * Cfg::M0MAX + a] = acc;
+        if (args.importance && t0 + i < args.n_tiles)
+          args.importance[((size_t)bh * args.n_tiles + t0 + i) * M0 + a] = acc;
       }
     }
   };
@@ -948,7 +989,7 @@ void attention_kernel(AttnArgs args) {
   __syncthreads();
 
   // ---- phase 3: top-P (w desc, index asc) -------------------------------------
-  // One wave. Lane l holds the keys of parents 64 i + l: the importance bits
+  // One wave per tile. Lane l holds the keys of parents 64 i + l: the importance bits
   // plus one (importance is a non-negative float, so the integer order is the
   // value order; padding gets 0, below every parent). A threshold kp is built
   // bit by bit from the top, the largest with at least P keys >= kp (the P-th
@@ -957,6 +998,8 @@ void attention_kernel(AttnArgs args) {
   // still missing. The selected parents are listed in index order. With
   // P >= M0 every parent is selected (all keys 1).
   if (P > 0) {
+    const float* lwf = lwf_all + sub * Cfg::M0MAX;
+    int* sel_out = lsel_all + sub * Cfg::M0MAX;
     // NV key registers per lane: the fewest that hold M0 parents
     auto select_top = [&](auto nv_tag) {
       constexpr int NV = decltype(nv_tag)::value;
@@ -992,18 +1035,19 @@ void attention_kernel(AttnArgs args) {
         const bool sel = key[i] > kp || (eq && eq_before + __popcll(me & below) < need);
         eq_before += __popcll(me);
         const unsigned long long ms = __ballot(sel);
-        if (sel) lsel[filled + __popcll(ms & below)] = kWave * i + lane;
+        if (sel) sel_out[filled + __popcll(ms & below)] = kWave * i + lane;
         filled += __popcll(ms);
       }
     };
-    if (wave == 0) {
+    if (wave % Cfg::WPT == 0) {
       if (M0 <= 2 * kWave) select_top(std::integral_constant<int, 2>{});
       else if (M0 <= 4 * kWave) select_top(std::integral_constant<int, 4>{});
       else select_top(std::integral_constant<int, Cfg::M0MAX / kWave>{});
     }
     __syncthreads();
     if (args.topp_idx) {  // canonical order (w desc, index asc) for the caller
-      for (int q = tid; q < P; q += blockDim.x) {
+      constexpr int TT = Cfg::WPT * kWave;  // threads of a tile
+      for (int q = tid % TT; q < P && t < args.n_tiles; q += TT) {
         const int a = lsel[q];
         const float wa = lwf[a];
         int rank = 0;
@@ -1020,13 +1064,15 @@ void attention_kernel(AttnArgs args) {
     // The selected parents' child octets, 8 per chunk. With one child the
     // recovered parent logit is that child's own logit, so every correcting
     // weight is exactly zero: nothing to do.
-    const int n_cchunks = (n_child_oct + 7) / 8;
+    const int n_cchunks = (n_child_oct + OPT - 1) / OPT;
     if (n_cchunks > 0) issue_child(0, 0);
     for (int k = 0; k < n_cchunks; ++k) {
       wait_chunk();
       if (Cfg::NBUF == 2 && k + 1 < n_cchunks) issue_child(k + 1, (k + 1) % 2);
       const unsigned char* B = buffer(k % Cfg::NBUF);
-      if (has_rows && half_child) {
+      if (TPW == 2) {  // the tile's pair of the chunk
+        if (has_rows) child_pair(B, sub);
+      } else if (has_rows && half_child) {
         child_chunk_half(B);
       } else if (has_rows) {
         f32x4 S0[2][QS], S1[2][QS];
@@ -1128,19 +1174,47 @@ void attention_kernel(AttnArgs args) {
   }
 }
 
-template <typename T, int D, int MAXW, bool TILED>
+template <typename T, int D, int MAXW, int TPW, bool TILED>
 hipError_t launch_attention_cfg(const AttnArgs& a, int BH, hipStream_t stream) {
-  const long long grid = (long long)BH * a.n_tiles;
+  const long long grid = (long long)BH * ((a.n_tiles + TPW - 1) / TPW);
   if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;
-  using Cfg = AttnCfg<T, D, MAXW>;
+  using Cfg = AttnCfg<T, D, MAXW, TPW>;
   constexpr int slot = (TILED ? 48 : 8) + (Elem<T>::kBf16 ? 0 : 4) + (D == 128 ? 2 : 0) +
-                       (MAXW == 8 ? 1 : 0);
-  hipError_t e = ensure_dynamic_lds((const void*)attention_kernel<T, D, MAXW, TILED>,
+                       (MAXW == 8 ? 1 : 0) + (TPW == 2 ? (MAXW == 4 ? 180 : 188) - 8 : 0);
+  hipError_t e = ensure_dynamic_lds((const void*)attention_kernel<T, D, MAXW, TPW, TILED>,
                                     (int)Cfg::LDS_BYTES, slot);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attention_kernel<T, D, MAXW, TILED>), dim3((unsigned)grid),
+  hipLaunchKernelGGL((attention_kernel<T, D, MAXW, TPW, TILED>), dim3((unsigned)grid),
                      dim3(MAXW * 64), Cfg::LDS_BYTES, stream, a);
   return hipGetLastError();
+}
+
+// Query blocks of at most 64 fill one or two waves, so two tiles share a
+// workgroup, its copies of the parent chunks and the child chunks (one tile
+// pair each), where that beats one tile per 4-wave workgroup with idle waves:
+// once the single tiles no longer all run at once (resident per CU), and for
+// two-wave tiles also while they would be two per CU. us, one / two tiles per
+// workgroup (M0 = 256, Ch = 8, P = 32, bf16, d = 128, 256 CUs): blocks of 64,
+// 256 tiles 20.8 / 23.2, 384 26.8 / 23.8, 768 41.9 / 32.4, 1024 50.1 / 34.7;
+// blocks of 32, 512 tiles 22.1 / 25.1, 768 38.3 / 32.5; d = 64 (three per
+// CU), blocks of 64, 512 tiles 21.1 / 19.0, 768 23.8 / 24.7, 1024 34.3 / 25.1;
+// blocks of 32, 768 tiles 18.4 / 23.3, 1024 30.0 / 23.0.
+template <typename T, int D, bool TILED>
+hipError_t launch_attention_tiles(const AttnArgs& a, int BH, hipStream_t stream) {
+  if (a.block_q <= 64) {
+    DeviceInfo dev;
+    const hipError_t e = device_info(&dev);
+    if (e != hipSuccess) return e;
+    const long long cus = dev.cus > 1 ? dev.cus : 1, tiles = (long long)BH * a.n_tiles;
+    const bool all_at_once = tiles <= AttnCfg<T, D, 4, 1>::kWavesPerEu * cus;
+    if (a.block_q <= 32) {
+      if (!all_at_once) return launch_attention_cfg<T, D, 2, 2, TILED>(a, BH, stream);
+    } else if (!all_at_once || (tiles > cus && tiles <= 2 * cus)) {
+      return launch_attention_cfg<T, D, 4, 2, TILED>(a, BH, stream);
+    }
+  }
+  if (a.block_q <= 128) return launch_attention_cfg<T, D, 4, 1, TILED>(a, BH, stream);
+  return launch_attention_cfg<T, D, 8, 1, TILED>(a, BH, stream);
 }
 
 template <typename T, int D>
@@ -1164,12 +1238,8 @@ hipError_t launch_attention(int BH, int H, int N, int M0, int Ch, int P, int blo
   a.P = P;
   a.block_q = block_q;
   a.n_tiles = (N + block_q - 1) / block_q;
-  if (tiled) {
-    if (block_q <= 128) return launch_attention_cfg<T, D, 4, true>(a, BH, stream);
-    return launch_attention_cfg<T, D, 8, true>(a, BH, stream);
-  }
-  if (block_q <= 128) return launch_attention_cfg<T, D, 4, false>(a, BH, stream);
-  return launch_attention_cfg<T, D, 8, false>(a, BH, stream);
+  return tiled ? launch_attention_tiles<T, D, true>(a, BH, stream)
+               : launch_attention_tiles<T, D, false>(a, BH, stream);
 }
 
 #define AVQ_INSTANTIATE(T, D)                                                                \
