@@ -14,8 +14,8 @@
 //
 // parent_stream_kernel (below) when the head's parent codebook fits the LDS
 // (always for bf16); otherwise (fp32 codebooks of more rows)
-// parent_assign_kernel: one workgroup = 256 keys of one (batch, head), 4
-// waves of 64 keys. The norms of the head's parents are summed once per
+// parent_assign_kernel: one workgroup = 128 keys of one (batch, head), 8
+// waves of 16 keys. The norms of the head's parents are summed once per
 // workgroup (one row per thread, in order); the parent codebook streams
 // through LDS in chunks of 64 rows by direct global->LDS copies, double
 // buffered. Every lane keeps a running (distance, index) minimum over its
@@ -56,8 +56,13 @@ __device__ __forceinline__ void copy16_lds(const void* src, void* lds) {
 // fp32 only (a bf16 codebook of up to 512 rows always fits the stream kernel)
 template <int D>
 struct AssignCfg {
-  static constexpr int kWaves = 4;
-  static constexpr int KS = 4;                    // key subtiles (of 16) per wave
+  // 8 waves of 16 keys: four waves per SIMD at two workgroups per CU, and small
+  // launches spread over the CUs. Rows and keys load 16 bytes per lane (four
+  // k-steps). 8 heads of 4096 keys, 256 x 128 parents: 57 -> 28 us against 4
+  // waves of 64 keys with 4-byte operands (128 workgroups, one wave per SIMD
+  // on half of the CUs)
+  static constexpr int kWaves = 8;
+  static constexpr int KS = 1;                    // key subtiles (of 16) per wave
   static constexpr int kKeysPerBlock = kWaves * KS * 16;
   static constexpr int CW = 64;                   // codebook rows per chunk
   static constexpr int KQ = D / 4;                // MFMA k-steps over d
@@ -118,15 +123,14 @@ __global__ __launch_bounds__((AssignCfg<D>::kWaves * 64)) void parent_assign_ker
     lnorm[r] = acc;
   }
 
-  // key fragments: subtile s holds key key0 + 16 s + c; lane group g holds
-  // the d values of k-step kq at 4 kq + g
+  // key fragments: subtile s holds key key0 + 16 s + c, in row_frags' order
   float kf[KS][KQ];
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
     const int j = key0 + 16 * s + c;
-    const T* row = K + ((size_t)bh * N + (j < N ? j : 0)) * D;
+    row_frags<T, D>(K + ((size_t)bh * N + (j < N ? j : 0)) * D, g, kf[s]);
 #pragma unroll
-    for (int kq = 0; kq < KQ; ++kq) kf[s][kq] = times_minus2((j < N) ? row[4 * kq + g] : 0.f);
+    for (int kq = 0; kq < KQ; ++kq) kf[s][kq] = times_minus2((j < N) ? kf[s][kq] : 0.f);
   }
 
   float best[KS];
@@ -151,10 +155,13 @@ __global__ __launch_bounds__((AssignCfg<D>::kWaves * 64)) void parent_assign_ker
       const f32x4 nr = *reinterpret_cast<const f32x4*>(&lnorm[CW * k + 16 * tt + 4 * g]);
       f32x4 acc[KS];
 #pragma unroll
-      for (int kq = 0; kq < KQ; ++kq) {
-        const float a = lc[r * D + (kq ^ sw) * EPU + g];
+      for (int q = 0; q < KQ / 4; ++q) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(&lc[r * D + ((4 * q + g) ^ sw) * EPU]);
 #pragma unroll
-        for (int s = 0; s < KS; ++s) acc[s] = mfma_f32(a, kf[s][kq], kq == 0 ? nr : acc[s]);
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int s = 0; s < KS; ++s)
+            acc[s] = mfma_f32(a[e], kf[s][4 * q + e], q + e == 0 ? nr : acc[s]);
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -187,7 +194,7 @@ __global__ __launch_bounds__((AssignCfg<D>::kWaves * 64)) void parent_assign_ker
 // ---------------------------------------------------------------------------
 // parent_stream_kernel: the same argmin when the head's whole parent codebook
 // fits the LDS (bf16: one 16-wave workgroup per CU, up to 150 KB, every
-// supported codebook; fp32: two 4-wave workgroups per CU, half the LDS
+// supported codebook; fp32: two 8-wave workgroups per CU, half the LDS
 // each). Each workgroup is persistent over a run of consecutive steps
 // (normally of one (batch, head)): the codebook and its norms are staged once
 // per head, and the key fragments of the next step load while the current
@@ -198,11 +205,13 @@ template <typename T, int D>
 struct StreamCfg {
   static constexpr bool kB = Elem<T>::kBf16;
   // bf16: 16 waves of 32 keys (under 128 VGPRs, four waves per SIMD); fp32:
-  // 4 waves of 64 keys (its fragments need the registers of two waves per
-  // SIMD) and two workgroups per CU
-  static constexpr int kWaves = kB ? 16 : 4;
+  // 8 waves of 16 keys, two workgroups per CU, operands of 16 bytes per lane
+  // (against 4 waves of 64 keys and 4-byte operands: 1024 keys of d = 64, 32
+  // parents, 13.4 -> 5.5 us; the precompute of 4 heads of 41803 keys, d = 128,
+  // 128 parents, 252 -> 106 us)
+  static constexpr int kWaves = kB ? 16 : 8;
   static constexpr int kPerCU = kB ? 1 : 2;       // workgroups per CU
-  static constexpr int KS = kB ? 2 : 4;           // key subtiles (of 16) per wave
+  static constexpr int KS = kB ? 2 : 1;           // key subtiles (of 16) per wave
   static constexpr int kKeysPerStep = kWaves * KS * 16;
   static constexpr int KQ = kB ? D / 32 : D / 4;
   static constexpr int ESZ = sizeof(T);
@@ -216,7 +225,8 @@ struct StreamCfg {
 };
 
 template <typename T, int D>
-__global__ __launch_bounds__((StreamCfg<T, D>::kWaves * 64)) void parent_stream_kernel(
+__global__ __launch_bounds__((StreamCfg<T, D>::kWaves * 64))
+__attribute__((amdgpu_waves_per_eu(4))) void parent_stream_kernel(
     const T* __restrict__ K, const T* __restrict__ Cp, int32_t* __restrict__ parent_idx,
     int32_t* __restrict__ code_idx, int H, int N, int M0, int steps_per_bh, int n_steps) {
   using Cfg = StreamCfg<T, D>;
@@ -238,23 +248,15 @@ __global__ __launch_bounds__((StreamCfg<T, D>::kWaves * 64)) void parent_stream_
   const int s_begin = wg * per, s_end = min(s_begin + per, n_steps);
   if (s_begin >= s_end) return;  // whole workgroup
 
-  // raw key fragments of step st: subtile s holds key key0 + 16 s + c, lane
-  // group g the d values of k-step kq at 32 kq + 8 g (bf16) or 4 kq + g (fp32);
-  // keys past N read key N - 1
+  // raw key fragments of step st: subtile s holds key key0 + 16 s + c, in
+  // row_frags' order; keys past N read key N - 1
   auto load_keys = [&](int st, Frag (&dst)[KS][KQ]) {
     const int bh = st / steps_per_bh;
     const int key0 = (st % steps_per_bh) * Cfg::kKeysPerStep + wave * KS * 16;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int j = min(key0 + 16 * s + c, N - 1);
-      const T* row = K + ((size_t)bh * N + j) * D;
-#pragma unroll
-      for (int kq = 0; kq < KQ; ++kq) {
-        if constexpr (kB)
-          dst[s][kq] = *reinterpret_cast<const bf16x8*>(row + 32 * kq + 8 * g);
-        else
-          dst[s][kq] = row[4 * kq + g];
-      }
+      row_frags<T, D>(K + ((size_t)bh * N + j) * D, g, dst[s]);
     }
   };
 
@@ -326,33 +328,45 @@ __global__ __launch_bounds__((StreamCfg<T, D>::kWaves * 64)) void parent_stream_
     // tile's comparisons
     for (int tt = 0; tt < M16 / 16; tt += 2) {
       f32x4 acc[2][KS];
-      Frag a[2][KQ];
       f32x4 nr[2];
-#pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2) {
-        const int r = 16 * (tt + h2) + c;
-        const int sw = assign_swizzle<U>(r);
-        // the accumulator starts at -||c||^2 / 2 of the lane's rows
-        nr[h2] = *reinterpret_cast<const f32x4*>(&lnorm[16 * (tt + h2) + 4 * g]);
-#pragma unroll
-        for (int kq = 0; kq < KQ; ++kq) {
-          if constexpr (kB)
-            a[h2][kq] = *reinterpret_cast<const bf16x8*>(&lc[r * D + ((4 * kq + g) ^ sw) * EPU]);
-          else
-            a[h2][kq] = lc[r * D + (kq ^ sw) * EPU + g];
-        }
-      }
+      const int sw = assign_swizzle<U>(c);  // of rows 16 t + c, any t
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2)
+        // the accumulator starts at -||c||^2 / 2 of the lane's rows
+        nr[h2] = *reinterpret_cast<const f32x4*>(&lnorm[16 * (tt + h2) + 4 * g]);
+      if constexpr (kB) {
+        Frag a[2][KQ];
 #pragma unroll
-        for (int kq = 0; kq < KQ; ++kq)
+        for (int h2 = 0; h2 < 2; ++h2) {
+          const int r = 16 * (tt + h2) + c;
 #pragma unroll
-          for (int s = 0; s < KS; ++s) {
-            if constexpr (kB)
+          for (int kq = 0; kq < KQ; ++kq)
+            a[h2][kq] = *reinterpret_cast<const bf16x8*>(&lc[r * D + ((4 * kq + g) ^ sw) * EPU]);
+        }
+#pragma unroll
+        for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+          for (int kq = 0; kq < KQ; ++kq)
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
               acc[h2][s] = mfma_bf16(a[h2][kq], kf[s][kq], kq == 0 ? nr[h2] : acc[h2][s]);
-            else
-              acc[h2][s] = mfma_f32(a[h2][kq], kf[s][kq], kq == 0 ? nr[h2] : acc[h2][s]);
-          }
+      } else {
+#pragma unroll
+        for (int q = 0; q < KQ / 4; ++q) {
+          f32x4 a[2];
+#pragma unroll
+          for (int h2 = 0; h2 < 2; ++h2)
+            a[h2] = *reinterpret_cast<const f32x4*>(
+                &lc[(16 * (tt + h2) + c) * D + ((4 * q + g) ^ sw) * EPU]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+              for (int s = 0; s < KS; ++s)
+                acc[h2][s] = mfma_f32(a[h2][e], kf[s][4 * q + e], q + e == 0 ? nr[h2] : acc[h2][s]);
+        }
+      }
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2)
 #pragma unroll

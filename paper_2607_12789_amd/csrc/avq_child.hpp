@@ -55,25 +55,40 @@ struct ChildTile {
   using Frag = typename std::conditional<kB, bf16x8, float>::type;
 };
 
+// A row's values of lane group g as MFMA k-steps: bf16, k-step kq at d = 32 kq
+// + 8 g; fp32, k-step 4 q + e at d = 16 q + 4 g + e, so that four k-steps are
+// one 16-byte load (both operands of a product take the same order of d).
+template <typename T, int D>
+__device__ __forceinline__ void row_frags(
+    const T* __restrict__ row, int g,
+    typename std::conditional<Elem<T>::kBf16, bf16x8, float>::type (
+        &f)[Elem<T>::kBf16 ? D / 32 : D / 4]) {
+  if constexpr (Elem<T>::kBf16) {
+#pragma unroll
+    for (int kq = 0; kq < D / 32; ++kq)
+      f[kq] = *reinterpret_cast<const bf16x8*>(row + 32 * kq + 8 * g);
+  } else {
+#pragma unroll
+    for (int q = 0; q < D / 16; ++q) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(row + 16 * q + 4 * g);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[4 * q + e] = v[e];
+    }
+  }
+}
+
 // The candidate rows of parent p of head h (A operand): lane (g, c) holds row
-// c of each tile, k-step kq at d = 32 kq + 8 g (bf16) or 4 kq + g (fp32).
+// c of each tile, in row_frags' order.
 template <typename T, int D, int NT>
 __device__ __forceinline__ void child_rows_load(
     const T* __restrict__ Cp, const T* __restrict__ Cc, int h, int M0, int Ch, int p, int g,
     int c, typename ChildTile<T, D, NT>::Frag (&cf)[NT][ChildTile<T, D, NT>::KQ]) {
-  constexpr int KQ = ChildTile<T, D, NT>::KQ;
 #pragma unroll
   for (int t2 = 0; t2 < NT; ++t2) {
     const int cand = 16 * t2 + c;
     const T* row = cand == 0 ? Cp + ((size_t)h * M0 + p) * D
                              : Cc + (((size_t)h * M0 + p) * Ch + min(cand - 1, Ch - 1)) * D;
-#pragma unroll
-    for (int kq = 0; kq < KQ; ++kq) {
-      if constexpr (Elem<T>::kBf16)
-        cf[t2][kq] = *reinterpret_cast<const bf16x8*>(row + 32 * kq + 8 * g);
-      else
-        cf[t2][kq] = row[4 * kq + g];
-    }
+    row_frags<T, D>(row, g, cf[t2]);
   }
 }
 
@@ -112,14 +127,7 @@ __device__ __forceinline__ void child_rows(
 template <typename T, int D, int NT>
 __device__ __forceinline__ void child_key(const T* __restrict__ krow, int g,
                                           typename ChildTile<T, D, NT>::Frag (&kf)[ChildTile<T, D, NT>::KQ]) {
-  constexpr int KQ = ChildTile<T, D, NT>::KQ;
-#pragma unroll
-  for (int kq = 0; kq < KQ; ++kq) {
-    if constexpr (Elem<T>::kBf16)
-      kf[kq] = *reinterpret_cast<const bf16x8*>(krow + 32 * kq + 8 * g);
-    else
-      kf[kq] = krow[4 * kq + g];
-  }
+  row_frags<T, D>(krow, g, kf);
 }
 
 // The family-local row of the key in column c: 0 if the parent stays, else
