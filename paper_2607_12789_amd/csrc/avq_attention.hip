@@ -2,7 +2,7 @@
 //
 // One workgroup processes one query tile (block_q consecutive tokens of one
 // (batch, head)), or two tiles of at most 64 queries; each wave owns 32 query
-// rows. Everything is computed
+// rows (fp32: 16). Everything is computed
 // transposed, codewords x queries: S^T = C . Q^T and Xbar^T = Vmean^T . W^T,
 // with 16x16x32 bf16 (16x16x4 fp32) MFMA. A lane owns one query column and,
 // in a pair of 16-row logit tiles, 8 consecutive codes (one octet of the
@@ -71,12 +71,12 @@
 
 namespace avq {
 
-// TPW: query tiles per workgroup, each with MAXW / TPW waves
-template <typename T, int D, int MAXW, int TPW>
+// TPW: query tiles per workgroup, each with MAXW / TPW waves of RPW_ queries
+template <typename T, int D, int MAXW, int TPW, int RPW_>
 struct AttnCfg {
   static constexpr int WPT = MAXW / TPW;          // waves per tile
   static constexpr bool kB = Elem<T>::kBf16;
-  static constexpr int RPW = 32;                  // query rows per wave (16 QS)
+  static constexpr int RPW = RPW_;                // query rows per wave (16 QS)
   static constexpr int QS = RPW / 16;             // query subtiles per wave
   static constexpr int CW = 64;                   // codeword rows per chunk
   static constexpr int TPC = CW / 16;             // 16-row tiles per chunk
@@ -102,7 +102,13 @@ struct AttnCfg {
   static constexpr size_t OFF_WF = OFF_LW + 2 * MAXW * CW * 4;  // [TPW][M0MAX] f32
   static constexpr size_t OFF_SEL = OFF_WF + TPW * M0MAX * 4;   // [TPW][M0MAX] i32
   static constexpr size_t LDS_BYTES = OFF_SEL + TPW * M0MAX * 4;
-  static constexpr int kWavesPerEu = (kB && D == 64) ? 3 : 2;  // 4-wave workgroups per CU
+  // waves per SIMD: bf16 three at d = 64 (registers), two at d = 128; fp32 four,
+  // but two for 4-wave workgroups at d = 128 (LDS for two workgroups per CU).
+  // fp32 d = 128, 8 waves: four spill 18 registers outside the loops but are
+  // faster than two (16 x 8192 in blocks of 128: 329 against 366 us, and 355
+  // with two chunk buffers)
+  static constexpr int kWavesPerEu =
+      !kB && RPW == 16 ? (D == 64 || MAXW >= 8 ? 4 : 2) : (kB && D == 64) ? 3 : 2;
   static_assert(COPIES % MAXW == 0 || COPIES < MAXW, "copies split evenly over the waves");
   static_assert(OCPY >= 1 && (OCPY & (OCPY - 1)) == 0, "whole wave copies per octet");
 };
@@ -138,11 +144,11 @@ __device__ __forceinline__ int row_swizzle(int r) {
 // each), so that other tiles' MFMA work runs while one workgroup waits.
 // TILED: importance with the count-extrapolated denominator of App. B, one
 // codeword tile per chunk, computed in the parent sweep (no second sweep).
-template <typename T, int D, int MAXW, int TPW, bool TILED>
+template <typename T, int D, int MAXW, int TPW, int RPW, bool TILED>
 __global__ __launch_bounds__(MAXW * 64)
-__attribute__((amdgpu_waves_per_eu(AttnCfg<T, D, MAXW, TPW>::kWavesPerEu)))
+__attribute__((amdgpu_waves_per_eu(AttnCfg<T, D, MAXW, TPW, RPW>::kWavesPerEu)))
 void attention_kernel(AttnArgs args) {
-  using Cfg = AttnCfg<T, D, MAXW, TPW>;
+  using Cfg = AttnCfg<T, D, MAXW, TPW, RPW>;
   constexpr bool kB = Cfg::kB;
   constexpr int QS = Cfg::QS, CW = Cfg::CW, TPC = Cfg::TPC, KQ = Cfg::KQ, DT = Cfg::DT,
                 U = Cfg::U, EPU = Cfg::EPU, CPW = Cfg::CPW,
@@ -212,9 +218,10 @@ void attention_kernel(AttnArgs args) {
       if constexpr (kB) {
         bf16x8 v = *reinterpret_cast<const bf16x8*>(qrow + 32 * kq + 8 * g);
         qf[s][kq] = qvalid[s] ? v : bf16x8{};
-      } else {
-        float v = qrow[4 * kq + g];
-        qf[s][kq] = qvalid[s] ? v : 0.f;
+      } else if (kq % 4 == 0) {  // k-step 4 q + e: d = 16 q + 4 g + e, four per load
+        const f32x4 v = *reinterpret_cast<const f32x4*>(qrow + 4 * kq + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) qf[s][kq + e] = qvalid[s] ? v[e] : 0.f;
       }
     }
   }
@@ -367,12 +374,14 @@ void attention_kernel(AttnArgs args) {
         for (int s = 0; s < QS; ++s)
           out[s] = qrows ? mfma_bf16(qf[s][kq], a, kq == 0 ? init : out[s])
                          : mfma_bf16(a, qf[s][kq], kq == 0 ? init : out[s]);
-      } else {
-        const float a = lc[r * D + (kq ^ sw) * EPU + g];
+      } else if (kq % 4 == 0) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(&lc[r * D + ((kq + g) ^ sw) * EPU]);
 #pragma unroll
-        for (int s = 0; s < QS; ++s)
-          out[s] = qrows ? mfma_f32(qf[s][kq], a, kq == 0 ? init : out[s])
-                         : mfma_f32(a, qf[s][kq], kq == 0 ? init : out[s]);
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int s = 0; s < QS; ++s)
+            out[s] = qrows ? mfma_f32(qf[s][kq + e], a[e], kq + e == 0 ? init : out[s])
+                           : mfma_f32(a[e], qf[s][kq + e], kq + e == 0 ? init : out[s]);
       }
     }
   };
@@ -1174,17 +1183,22 @@ void attention_kernel(AttnArgs args) {
   }
 }
 
-template <typename T, int D, int MAXW, int TPW, bool TILED>
+template <typename T, int D, int MAXW, int TPW, int RPW, bool TILED>
 hipError_t launch_attention_cfg(const AttnArgs& a, int BH, hipStream_t stream) {
   const long long grid = (long long)BH * ((a.n_tiles + TPW - 1) / TPW);
   if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;
-  using Cfg = AttnCfg<T, D, MAXW, TPW>;
-  constexpr int slot = (TILED ? 48 : 8) + (Elem<T>::kBf16 ? 0 : 4) + (D == 128 ? 2 : 0) +
-                       (MAXW == 8 ? 1 : 0) + (TPW == 2 ? (MAXW == 4 ? 180 : 188) - 8 : 0);
-  hipError_t e = ensure_dynamic_lds((const void*)attention_kernel<T, D, MAXW, TPW, TILED>,
+  using Cfg = AttnCfg<T, D, MAXW, TPW, RPW>;
+  // 8 .. 15 and 48 .. 55 one tile (MAXW 4, 8 of RPW 32), 180 .. and 220 .. two
+  // (MAXW 4, 2); fp32 waves of 16 queries 196 .. and 236 ..
+  constexpr int slot =
+      RPW == 16 ? (TILED ? 236 : 196) + (D == 128 ? 4 : 0) +
+                      (MAXW == 16 ? 3 : MAXW == 8 ? 1 : 0) + (TPW == 2 ? 2 : 0)
+                : (TILED ? 48 : 8) + (Elem<T>::kBf16 ? 0 : 4) + (D == 128 ? 2 : 0) +
+                      (MAXW == 8 ? 1 : 0) + (TPW == 2 ? (MAXW == 4 ? 180 : 188) - 8 : 0);
+  hipError_t e = ensure_dynamic_lds((const void*)attention_kernel<T, D, MAXW, TPW, RPW, TILED>,
                                     (int)Cfg::LDS_BYTES, slot);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attention_kernel<T, D, MAXW, TPW, TILED>), dim3((unsigned)grid),
+  hipLaunchKernelGGL((attention_kernel<T, D, MAXW, TPW, RPW, TILED>), dim3((unsigned)grid),
                      dim3(MAXW * 64), Cfg::LDS_BYTES, stream, a);
   return hipGetLastError();
 }
@@ -1201,20 +1215,36 @@ hipError_t launch_attention_cfg(const AttnArgs& a, int BH, hipStream_t stream) {
 // blocks of 32, 768 tiles 18.4 / 23.3, 1024 30.0 / 23.0.
 template <typename T, int D, bool TILED>
 hipError_t launch_attention_tiles(const AttnArgs& a, int BH, hipStream_t stream) {
-  if (a.block_q <= 64) {
-    DeviceInfo dev;
-    const hipError_t e = device_info(&dev);
-    if (e != hipSuccess) return e;
-    const long long cus = dev.cus > 1 ? dev.cus : 1, tiles = (long long)BH * a.n_tiles;
-    const bool all_at_once = tiles <= AttnCfg<T, D, 4, 1>::kWavesPerEu * cus;
+  DeviceInfo dev;
+  const hipError_t e = device_info(&dev);
+  if (e != hipSuccess) return e;
+  const long long cus = dev.cus > 1 ? dev.cus : 1, tiles = (long long)BH * a.n_tiles;
+  if constexpr (Elem<T>::kBf16) {
+    const bool all_at_once = tiles <= AttnCfg<T, D, 4, 1, 32>::kWavesPerEu * cus;
     if (a.block_q <= 32) {
-      if (!all_at_once) return launch_attention_cfg<T, D, 2, 2, TILED>(a, BH, stream);
-    } else if (!all_at_once || (tiles > cus && tiles <= 2 * cus)) {
-      return launch_attention_cfg<T, D, 4, 2, TILED>(a, BH, stream);
+      if (!all_at_once) return launch_attention_cfg<T, D, 2, 2, 32, TILED>(a, BH, stream);
+    } else if (a.block_q <= 64) {
+      if (!all_at_once || (tiles > cus && tiles <= 2 * cus))
+        return launch_attention_cfg<T, D, 4, 2, 32, TILED>(a, BH, stream);
     }
+    if (a.block_q <= 128) return launch_attention_cfg<T, D, 4, 1, 32, TILED>(a, BH, stream);
+    return launch_attention_cfg<T, D, 8, 1, 32, TILED>(a, BH, stream);
+  } else {
+    // fp32 waves hold 16 queries: half the registers of 32 (which took every
+    // register of two waves per SIMD, and spilled at d = 128), so twice the
+    // waves per tile and per SIMD; a product takes 32 cycles per wave, which
+    // the second read of the codewords hides behind. us, 32 / 16 queries per
+    // wave (M0 = 256, Ch = 8, P = 32): 8 heads x 4096 x 128, blocks of 64 165
+    // / 98, of 128 113 / 106; 16 x 8192 x 128, blocks of 128 343 / 327, of 200
+    // 525 / 485; d = 64: 189 / 174 and 286 / 259. Two tiles share a workgroup
+    // only for blocks of 32, once tiles outnumber two per CU (8 x 4096 x 64:
+    // 121 / 56 in all).
+    if (a.block_q <= 32 && tiles > 2 * cus)
+      return launch_attention_cfg<T, D, 4, 2, 16, TILED>(a, BH, stream);
+    if (a.block_q <= 64) return launch_attention_cfg<T, D, 4, 1, 16, TILED>(a, BH, stream);
+    if (a.block_q <= 128) return launch_attention_cfg<T, D, 8, 1, 16, TILED>(a, BH, stream);
+    return launch_attention_cfg<T, D, 16, 1, 16, TILED>(a, BH, stream);
   }
-  if (a.block_q <= 128) return launch_attention_cfg<T, D, 4, 1, TILED>(a, BH, stream);
-  return launch_attention_cfg<T, D, 8, 1, TILED>(a, BH, stream);
 }
 
 template <typename T, int D>
