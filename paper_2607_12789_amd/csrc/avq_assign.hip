@@ -201,7 +201,7 @@ __global__ __launch_bounds__((AssignCfg<D>::kWaves * 64)) void parent_assign_ker
 // step runs, so K streams from HBM without the gaps of a one-shot workgroup.
 // It keeps the keys unscaled and maximises k.c - ||c||^2 / 2, which is the
 // distance times -1/2 exactly.
-template <typename T, int D>
+template <typename T, int D, int WAVES>
 struct StreamCfg {
   static constexpr bool kB = Elem<T>::kBf16;
   // bf16: 16 waves of 32 keys (under 128 VGPRs, four waves per SIMD); fp32:
@@ -209,7 +209,7 @@ struct StreamCfg {
   // (against 4 waves of 64 keys and 4-byte operands: 1024 keys of d = 64, 32
   // parents, 13.4 -> 5.5 us; the precompute of 4 heads of 41803 keys, d = 128,
   // 128 parents, 252 -> 106 us)
-  static constexpr int kWaves = kB ? 16 : 8;
+  static constexpr int kWaves = WAVES;
   static constexpr int kPerCU = kB ? 1 : 2;       // workgroups per CU
   static constexpr int KS = kB ? 2 : 1;           // key subtiles (of 16) per wave
   static constexpr int kKeysPerStep = kWaves * KS * 16;
@@ -224,12 +224,12 @@ struct StreamCfg {
   static bool fits(int M0) { return lds_bytes(M0) <= LDS_CAP; }
 };
 
-template <typename T, int D>
-__global__ __launch_bounds__((StreamCfg<T, D>::kWaves * 64))
+template <typename T, int D, int WAVES>
+__global__ __launch_bounds__((StreamCfg<T, D, WAVES>::kWaves * 64))
 __attribute__((amdgpu_waves_per_eu(4))) void parent_stream_kernel(
     const T* __restrict__ K, const T* __restrict__ Cp, int32_t* __restrict__ parent_idx,
     int32_t* __restrict__ code_idx, int H, int N, int M0, int steps_per_bh, int n_steps) {
-  using Cfg = StreamCfg<T, D>;
+  using Cfg = StreamCfg<T, D, WAVES>;
   constexpr bool kB = Cfg::kB;
   constexpr int KS = Cfg::KS, KQ = Cfg::KQ, U = Cfg::U, EPU = Cfg::EPU;
   using Frag = typename std::conditional<kB, bf16x8, float>::type;
@@ -586,27 +586,49 @@ template <typename T, int D>
 hipError_t launch_assign(int BH, int H, int N, int M0, int Ch, const void* K, const void* Cp,
                          const void* Cc, int32_t* parent_idx, int32_t* code_idx,
                          bool with_children, hipStream_t stream) {
-  using SCfg = StreamCfg<T, D>;
   long long grid;
   DeviceInfo dev;
   hipError_t e = device_info(&dev);
   if (e != hipSuccess) return e;
-  if (SCfg::fits(M0)) {
+  const long long cus = dev.cus > 0 ? dev.cus : 1;
+  constexpr int kFull = Elem<T>::kBf16 ? 16 : 8;
+  if (StreamCfg<T, D, kFull>::fits(M0)) {
     // persistent: kPerCU workgroups per CU, each a run of whole steps
-    const int per_bh = (N + SCfg::kKeysPerStep - 1) / SCfg::kKeysPerStep;
-    const long long n_steps = (long long)BH * per_bh;
-    if (n_steps > 0x7fffffff) return hipErrorInvalidConfiguration;
-    const long long slots = (long long)SCfg::kPerCU * (dev.cus > 0 ? dev.cus : 1);
-    const long long per = (n_steps + slots - 1) / slots;
-    grid = (n_steps + per - 1) / per;
-    const int lds = SCfg::lds_bytes(M0);
-    constexpr int slot_s = 32 + (Elem<T>::kBf16 ? 0 : 2) + (D == 128 ? 1 : 0);
-    e = ensure_dynamic_lds((const void*)parent_stream_kernel<T, D>, SCfg::LDS_CAP, slot_s);
+    auto launch_stream = [&](auto waves_tag) {
+      constexpr int WAVES = decltype(waves_tag)::value;
+      using SCfg = StreamCfg<T, D, WAVES>;
+      const int per_bh = (N + SCfg::kKeysPerStep - 1) / SCfg::kKeysPerStep;
+      const long long n_steps = (long long)BH * per_bh;
+      if (n_steps > 0x7fffffff) return hipErrorInvalidConfiguration;
+      const long long slots = SCfg::kPerCU * cus;
+      const long long per = (n_steps + slots - 1) / slots;
+      grid = (n_steps + per - 1) / per;
+      const int lds = SCfg::lds_bytes(M0);
+      constexpr int slot_s = 32 + (Elem<T>::kBf16 ? 0 : 2) + (D == 128 ? 1 : 0) +
+                             (WAVES == kFull ? 0 : 4);
+      hipError_t err =
+          ensure_dynamic_lds((const void*)parent_stream_kernel<T, D, WAVES>, SCfg::LDS_CAP, slot_s);
+      if (err != hipSuccess) return err;
+      hipLaunchKernelGGL((parent_stream_kernel<T, D, WAVES>), dim3((unsigned)grid),
+                         dim3(SCfg::kWaves * kWave), lds, stream, static_cast<const T*>(K),
+                         static_cast<const T*>(Cp), parent_idx, Ch == 0 ? code_idx : nullptr, H,
+                         N, M0, per_bh, (int)n_steps);
+      return hipSuccess;
+    };
+    // bf16 at d = 128: 8 waves (256 keys) where all such steps run at once. A
+    // step's chain (keys, codebook, norms, tiles) then sets the time, and half
+    // the keys per workgroup halve its share of the loads and products.
+    // Precompute in us, 16 / 8 waves: 8 x 8192 keys, 512 parents 34.3 / 28.9; 10
+    // x 5003, 100 parents 42.0 / 39.1; 1 x 65536, 64 parents 42.9 / 40.8; with
+    // more steps (12 x 8192, 256 parents) 33.1 / 33.5. At d = 64 no difference
+    // (48 x 1024, 64 parents: 29.1 / 29.2 per whole step).
+    constexpr int kHalf = Elem<T>::kBf16 && D == 128 ? 8 : kFull;
+    const long long half_steps = (long long)BH * ((N + 255) / 256);
+    if (kHalf != kFull && half_steps <= cus)
+      e = launch_stream(std::integral_constant<int, kHalf>{});
+    else
+      e = launch_stream(std::integral_constant<int, kFull>{});
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((parent_stream_kernel<T, D>), dim3((unsigned)grid),
-                       dim3(SCfg::kWaves * kWave), lds, stream,
-                       static_cast<const T*>(K), static_cast<const T*>(Cp), parent_idx,
-                       Ch == 0 ? code_idx : nullptr, H, N, M0, per_bh, (int)n_steps);
   } else if constexpr (!Elem<T>::kBf16) {
     using Cfg = AssignCfg<D>;
     const int per_bh = (N + Cfg::kKeysPerBlock - 1) / Cfg::kKeysPerBlock;
