@@ -9,6 +9,7 @@ built, every call raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from pathlib import Path
 from typing import Optional
@@ -81,16 +82,20 @@ def _check(status: int) -> None:
         raise AvqError(status, lib().avq_last_error().decode())
 
 
+# Addresses are passed as integers: the argument types convert them, without
+# a pointer object per argument.
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream) -> int:
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _dev(t: torch.Tensor, name: str, dtype=None, shape=None):
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous()
+            and (dtype is None or t.dtype == dtype) and (shape is None or t.shape == shape)):
+        return t
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a tensor on the GPU")
     if not t.is_contiguous():
@@ -126,11 +131,16 @@ def assign(K, Cp, Cc, parent_idx=None, code_idx=None, stream=None):
     return parent_idx, code_idx
 
 
+@functools.lru_cache(maxsize=256, typed=True)
+def _packed_bytes(dtype_code: int, M0: int, Ch: int, d: int) -> int:
+    return lib().avq_packed_bytes(dtype_code, M0, Ch, d)
+
+
 def packed_bytes(dtype: torch.dtype, M0: int, Ch: int, d: int) -> int:
     """Bytes of the packed aggregates of one (batch, head)."""
     if dtype not in _DTYPES:
         raise ValueError(f"unsupported dtype {dtype}: use float32 or bfloat16")
-    n = lib().avq_packed_bytes(_DTYPES[dtype], M0, Ch, d)
+    n = _packed_bytes(_DTYPES[dtype], M0, Ch, d)
     if n < 0:
         raise ValueError(f"invalid sizes M0={M0} Ch={Ch} d={d}")
     return n
