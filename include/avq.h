@@ -143,8 +143,9 @@ int64_t avq_packed_bytes(avq_dtype_t dtype, int32_t M0, int32_t Ch, int32_t d);
  *             means first, info right after it.
  * At least one of Vbar and packed must be given.
  *
- * Every sum is accumulated in fp32 by the one half wave that owns the parent
- * family, keys in bucket order; counts are exact.
+ * Every sum is accumulated in fp32 by the one workgroup that owns the parent
+ * family (matrix products with 0 and 1, in no fixed key order); counts are
+ * exact.
  */
 avq_status_t avq_aggregate(avq_dtype_t dtype, int32_t B, int32_t H, int32_t N, int32_t d,
                            int32_t M0, int32_t Ch, const void* V, const int32_t* code_idx,
@@ -161,8 +162,8 @@ avq_status_t avq_aggregate(avq_dtype_t dtype, int32_t B, int32_t H, int32_t N, i
  * Vbar and packed within fp32 summation-order rounding. Two launches: the
  * parent assignment (it writes parent_idx, which the second launch reads),
  * then the child compare and aggregation per (batch, head, range of parent
- * families). Ch = 0 and Ch = 16 run avq_assign's two kernels and then
- * avq_aggregate's.
+ * families). Ch = 0, and fp32 with Ch = 16 at d = 128, run avq_assign's
+ * kernels and then avq_aggregate's.
  *
  *   K, V         [B][H][N][d]   dtype
  *   Cp           [H][M0][d]     dtype
