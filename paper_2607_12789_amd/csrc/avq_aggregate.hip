@@ -817,12 +817,10 @@ void aggregate_kernel(
 // 57.7 (chosen), 64 76.2; 32 heads of 256 (N = 16384, d = 128, 256 slots): 16
 // 104, 32 96 (chosen), 64 123.
 inline int families_per_workgroup(long long BH, int n_fam, long long slots) {
-  for (long long r = 1;; ++r) {
-    const long long ranges = r * slots / BH;  // per head
-    if (ranges < 1) continue;
-    const long long F = (n_fam + ranges - 1) / ranges;
-    if (F <= kMaxFamilies) return (int)F;
-  }
+  const long long least = (n_fam + kMaxFamilies - 1) / kMaxFamilies;  // ranges per head
+  const long long rounds = std::max(1LL, (least * BH + slots - 1) / slots);
+  const long long ranges = rounds * slots / BH;  // at least `least`
+  return (int)((n_fam + ranges - 1) / ranges);
 }
 
 template <typename T, int D, int NT, int MODE, bool SMALL>
