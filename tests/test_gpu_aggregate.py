@@ -118,3 +118,19 @@ def test_crowded_fused(dtype, d, Ch, keys):
         assert torch.equal(c_idx[0, h], c_idx[0, 0])
         check(V1, p_idx[0, h].long(), c_idx[0, h].long(), M0, Ch, packed[0, h], counts[0, h],
               Vbar[0, h])
+
+
+@pytest.mark.parametrize("N", [2 ** 21 - 3, 2 ** 21 + 5])
+def test_long_head(N):
+    """More keys than a compacted entry's key field holds (2^21), and the
+    longest ragged head below that."""
+    from paper_2607_12789_amd import avq
+    M0, Ch, d = 24, 4, 64
+    g = torch.Generator(device="cuda").manual_seed(11)
+    par = torch.randint(0, M0, (N,), device="cuda", generator=g)
+    child = torch.randint(-1, Ch, (N,), device="cuda", generator=g)
+    code = torch.where(child < 0, par, M0 + par * Ch + child)
+    V = torch.randn(N, d, device="cuda", generator=g).to(torch.bfloat16)
+    packed, counts, Vbar = avq.aggregate(V.view(1, 1, N, d), code.to(torch.int32).view(1, 1, N),
+                                         M0, Ch, sums=True)
+    check(V, par, code, M0, Ch, packed[0, 0], counts[0, 0], Vbar[0, 0])
