@@ -9,7 +9,6 @@ built, every call raises.
 from __future__ import annotations
 
 import ctypes
-import functools
 import os
 from pathlib import Path
 from typing import Optional
@@ -131,16 +130,11 @@ def assign(K, Cp, Cc, parent_idx=None, code_idx=None, stream=None):
     return parent_idx, code_idx
 
 
-@functools.lru_cache(maxsize=256, typed=True)
-def _packed_bytes(dtype_code: int, M0: int, Ch: int, d: int) -> int:
-    return lib().avq_packed_bytes(dtype_code, M0, Ch, d)
-
-
 def packed_bytes(dtype: torch.dtype, M0: int, Ch: int, d: int) -> int:
     """Bytes of the packed aggregates of one (batch, head)."""
     if dtype not in _DTYPES:
         raise ValueError(f"unsupported dtype {dtype}: use float32 or bfloat16")
-    n = _packed_bytes(_DTYPES[dtype], M0, Ch, d)
+    n = lib().avq_packed_bytes(_DTYPES[dtype], M0, Ch, d)
     if n < 0:
         raise ValueError(f"invalid sizes M0={M0} Ch={Ch} d={d}")
     return n

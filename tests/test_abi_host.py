@@ -8,7 +8,9 @@ import ctypes
 import re
 from pathlib import Path
 
+import numpy as np
 import pytest
+import torch
 
 from paper_2607_12789_amd import avq
 
@@ -109,6 +111,19 @@ def test_packed_size(L):
     assert L.avq_packed_bytes(BF16, 0, 2, 64) == -1
     assert L.avq_packed_bytes(BF16, 4, 2, -1) == -1
     assert L.avq_packed_bytes(7, 4, 2, 64) == -1
+
+
+def test_packed_bytes_takes_integer_objects(L):
+    """The sizes may be any object with an integer value, and the answer is of
+    that value at the call: a tensor changed in place gives its new size."""
+    want = [avq.packed_bytes(torch.bfloat16, m, 8, 64) for m in (64, 128)]
+    assert want[0] != want[1]
+    assert avq.packed_bytes(torch.bfloat16, np.int64(64), 8, 64) == want[0]
+    assert avq.packed_bytes(torch.bfloat16, np.array(64), np.array(8), 64) == want[0]
+    m0 = torch.tensor(64)
+    assert avq.packed_bytes(torch.bfloat16, m0, 8, 64) == want[0]
+    m0.fill_(128)
+    assert avq.packed_bytes(torch.bfloat16, m0, 8, 64) == want[1]
 
 
 def test_misaligned_pointers_are_rejected(L):
