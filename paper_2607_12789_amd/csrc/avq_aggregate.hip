@@ -104,7 +104,8 @@ struct AggCfg {
     int cursor[kMaxFamilies];      // keys scattered so far
     int spilled;                   // some wave's private list was too short
     float cell[kMaxFamilies];      // cell sizes (n of the parents)
-    uint16_t onehot[kWaves][NT][kGroup];  // row bits of the group's keys
+    // row bits of the group's keys, read as 16-byte vectors
+    alignas(16) uint16_t onehot[kWaves][NT][kGroup];
   };
   static constexpr int al16(int x) { return (x + 15) / 16 * 16; }
   static constexpr int OFF_SLOT = al16((int)sizeof(Tables));
