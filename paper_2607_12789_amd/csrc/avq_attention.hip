@@ -1203,30 +1203,58 @@ hipError_t launch_attention_cfg(const AttnArgs& a, int BH, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Query blocks of at most 64 fill one or two waves, so two tiles share a
-// workgroup, its copies of the parent chunks and the child chunks (one tile
-// pair each), where that beats one tile per 4-wave workgroup with idle waves:
-// once the single tiles no longer all run at once (resident per CU), and for
-// two-wave tiles also while they would be two per CU. us, one / two tiles per
-// workgroup (M0 = 256, Ch = 8, P = 32, bf16, d = 128, 256 CUs): blocks of 64,
-// 256 tiles 20.8 / 23.2, 384 26.8 / 23.8, 768 41.9 / 32.4, 1024 50.1 / 34.7;
-// blocks of 32, 512 tiles 22.1 / 25.1, 768 38.3 / 32.5; d = 64 (three per
-// CU), blocks of 64, 512 tiles 21.1 / 19.0, 768 23.8 / 24.7, 1024 34.3 / 25.1;
-// blocks of 32, 768 tiles 18.4 / 23.3, 1024 30.0 / 23.0.
+// Whether two query tiles share a workgroup. Query blocks of at most 64 fill
+// one or two waves, so a pair shares its workgroup's copies of the parent
+// chunks and the child chunks (one tile pair each), where that beats one tile
+// per 4-wave workgroup with idle waves: once the single tiles no longer all
+// run at once (resident per CU), and for two-wave tiles also while they would
+// be two per CU. us, one / two tiles per workgroup (M0 = 256, Ch = 8, P = 32,
+// bf16, d = 128, 256 CUs): blocks of 64, 256 tiles 20.8 / 23.2, 384 26.8 / 23.8,
+// 768 41.9 / 32.4, 1024 50.1 / 34.7; blocks of 32, 512 tiles 22.1 / 25.1, 768
+// 38.3 / 32.5; d = 64 (three per CU), blocks of 64, 512 tiles 21.1 / 19.0, 768
+// 23.8 / 24.7, 1024 34.3 / 25.1; blocks of 32, 768 tiles 18.4 / 23.3, 1024 30.0
+// / 23.0.
+//
+// With Ch = 2 or 4 a single tile takes the half of each child octet that holds
+// children (child_chunk_half), 8 parents per chunk; a pair takes whole octets,
+// 4 parents of each tile, so it loses where many parents are refined. It is
+// taken up to the share P / M0 where it still wins: lowest while the tiles are
+// one round, low where the pairs begin their second. One / two tiles in us, Ch =
+// 4, M0 = 256, about each line: one round (500 tiles, d = 64) P = 24 18.0 / 17.3,
+// 48 20.8 / 21.6; blocks of 32, pairs in one round, 800 tiles, P = 85 38.6 / 37.5
+// at d = 64, 53.0 / 52.5 at d = 128; in the next half round, 1600 tiles at d = 64,
+// P = 32 39.9 / 38.4, 48 44.7 / 45.8, 1200 at d = 128, P = 40 54.2 / 56.1; past it,
+// 4000 tiles, P = 75 109.2 / 104.9 at d = 64, 196.5 / 181.0 at d = 128; blocks of 64, d = 64, 2000 tiles, P = 75 69.4 / 62.2, 1600, P = 85 63.3 /
+// 65.2; d = 128 always (P = 85 107.1 / 94.9; M0 = 64, P = 64, 1000 tiles 39.6 /
+// 33.8). (Half octets in the pair's path cost its other Ch 3 to 11%.)
+//
+// fp32: only for blocks of 32, once tiles outnumber two per CU (8 heads x 4096
+// queries x 64: 121 us with one tile of 32-query waves, 56 now; with Ch = 4, P =
+// 170 of 256, 1200 tiles 296 / 230).
+template <typename T, int D>
+constexpr bool pair_tiles(int block_q, long long tiles, long long cus, int M0, int Ch, int P) {
+  if (!Elem<T>::kBf16) return block_q <= 32 && tiles > 2 * cus;
+  if (block_q > 64) return false;
+  const long long round = AttnCfg<T, D, 4, 1, 32>::kWavesPerEu * cus;  // workgroups at once
+  if (tiles <= round && (block_q <= 32 || tiles <= cus || tiles > 2 * cus)) return false;
+  if (Ch != 2 && Ch != 4) return true;
+  int share;
+  if (tiles <= round) share = 10;
+  else if (block_q > 32) share = D == 128 || tiles <= 2 * round ? 0 : 3;
+  else share = tiles <= 2 * round ? 3 : tiles <= 3 * round ? 8 : 3;
+  return P * share <= M0;
+}
+
 template <typename T, int D, bool TILED>
 hipError_t launch_attention_tiles(const AttnArgs& a, int BH, hipStream_t stream) {
   DeviceInfo dev;
   const hipError_t e = device_info(&dev);
   if (e != hipSuccess) return e;
   const long long cus = dev.cus > 1 ? dev.cus : 1, tiles = (long long)BH * a.n_tiles;
+  const bool pair = pair_tiles<T, D>(a.block_q, tiles, cus, a.M0, a.Ch, a.P);
   if constexpr (Elem<T>::kBf16) {
-    const bool all_at_once = tiles <= AttnCfg<T, D, 4, 1, 32>::kWavesPerEu * cus;
-    if (a.block_q <= 32) {
-      if (!all_at_once) return launch_attention_cfg<T, D, 2, 2, 32, TILED>(a, BH, stream);
-    } else if (a.block_q <= 64) {
-      if (!all_at_once || (tiles > cus && tiles <= 2 * cus))
-        return launch_attention_cfg<T, D, 4, 2, 32, TILED>(a, BH, stream);
-    }
+    if (pair && a.block_q <= 32) return launch_attention_cfg<T, D, 2, 2, 32, TILED>(a, BH, stream);
+    if (pair) return launch_attention_cfg<T, D, 4, 2, 32, TILED>(a, BH, stream);
     if (a.block_q <= 128) return launch_attention_cfg<T, D, 4, 1, 32, TILED>(a, BH, stream);
     return launch_attention_cfg<T, D, 8, 1, 32, TILED>(a, BH, stream);
   } else {
@@ -1236,11 +1264,8 @@ hipError_t launch_attention_tiles(const AttnArgs& a, int BH, hipStream_t stream)
     // the second read of the codewords hides behind. us, 32 / 16 queries per
     // wave (M0 = 256, Ch = 8, P = 32): 8 heads x 4096 x 128, blocks of 64 165
     // / 98, of 128 113 / 106; 16 x 8192 x 128, blocks of 128 343 / 327, of 200
-    // 525 / 485; d = 64: 189 / 174 and 286 / 259. Two tiles share a workgroup
-    // only for blocks of 32, once tiles outnumber two per CU (8 x 4096 x 64:
-    // 121 / 56 in all).
-    if (a.block_q <= 32 && tiles > 2 * cus)
-      return launch_attention_cfg<T, D, 4, 2, 16, TILED>(a, BH, stream);
+    // 525 / 485; d = 64: 189 / 174 and 286 / 259.
+    if (pair) return launch_attention_cfg<T, D, 4, 2, 16, TILED>(a, BH, stream);
     if (a.block_q <= 64) return launch_attention_cfg<T, D, 4, 1, 16, TILED>(a, BH, stream);
     if (a.block_q <= 128) return launch_attention_cfg<T, D, 8, 1, 16, TILED>(a, BH, stream);
     return launch_attention_cfg<T, D, 16, 1, 16, TILED>(a, BH, stream);
