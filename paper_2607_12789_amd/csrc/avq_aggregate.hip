@@ -676,16 +676,18 @@ void aggregate_kernel(
           }
           // sums^T += onehot . V (an empty family's only group: nothing)
           if (n > 0) {
+            // the one-hot rows as a bf16 operand; their product with ones is the
+            // counts (exact, and for fp32 one product instead of eight)
+            bf16x8 a[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+              uint32_t w[4];
+#pragma unroll
+              for (int q = 0; q < 4; ++q)  // bit c of both halves, as bf16 ones
+                w[q] = __umul24((oh[nt][q] >> c) & 0x00010001u, 0x3F80u);
+              __builtin_memcpy(&a[nt], w, 16);
+            }
             if constexpr (kB) {
-              bf16x8 a[NT];
-#pragma unroll
-              for (int nt = 0; nt < NT; ++nt) {
-                uint32_t w[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q)  // bit c of both halves, as bf16 ones
-                  w[q] = __umul24((oh[nt][q] >> c) & 0x00010001u, 0x3F80u);
-                __builtin_memcpy(&a[nt], w, 16);
-              }
 #pragma unroll
               for (int t = 0; t < CT; ++t) {
                 uint32_t w[4];
@@ -698,20 +700,23 @@ void aggregate_kernel(
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) acc[nt][t] = mfma_bf16(a[nt], b, acc[nt][t]);
               }
-              const bf16x8 ones = {(bf16)1.f, (bf16)1.f, (bf16)1.f, (bf16)1.f,
-                                   (bf16)1.f, (bf16)1.f, (bf16)1.f, (bf16)1.f};
+            }
+            const bf16x8 ones = {(bf16)1.f, (bf16)1.f, (bf16)1.f, (bf16)1.f,
+                                 (bf16)1.f, (bf16)1.f, (bf16)1.f, (bf16)1.f};
 #pragma unroll
-              for (int nt = 0; nt < NT; ++nt) an[nt] = mfma_bf16(a[nt], ones, an[nt]);
-            } else {
+            for (int nt = 0; nt < NT; ++nt) an[nt] = mfma_bf16(a[nt], ones, an[nt]);
+            if constexpr (!kB) {
+              // step j adds keys 4 j .. 4 j + 3: none past the group's n keys (a
+              // family of a few keys is mostly padding)
 #pragma unroll
               for (int j = 0; j < 8; ++j) {
+                if (4 * j >= n) break;
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
-                  const float a = (float)((oh[nt][j / 2] >> (c + 16 * (j % 2))) & 1u);
+                  const float x = (float)((oh[nt][j / 2] >> (c + 16 * (j % 2))) & 1u);
 #pragma unroll
                   for (int t = 0; t < CT; ++t)
-                    acc[nt][t] = mfma_f32(a, __uint_as_float(vr[j].w[t]), acc[nt][t]);
-                  an[nt] = mfma_f32(a, 1.f, an[nt]);
+                    acc[nt][t] = mfma_f32(x, __uint_as_float(vr[j].w[t]), acc[nt][t]);
                 }
               }
             }

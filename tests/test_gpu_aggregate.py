@@ -33,6 +33,9 @@ def crowded(M0, per_family, g):
 # among small ones, and 16 of about 3000 (together past every list)
 GIANT = [31, 32, 33, 0, 1, 30000, 0, 64, 65, 5, 0, 0, 17, 96, 2, 0]
 BATCHES = [3000 + 37 * (p % 3) for p in range(16)]
+# families of every size up to a whole group of keys and past it
+SIZES = list(range(40))
+KEYS = {"giant": GIANT, "batches": BATCHES, "sizes": SIZES}
 
 
 def reference(V, par, code, M0, Ch):
@@ -68,15 +71,15 @@ def check(V, par, code, M0, Ch, packed, counts, Vbar):
 
 
 @pytest.mark.parametrize("heads", [1, 256])  # 256: all 16 families in one workgroup
-@pytest.mark.parametrize("keys", ["giant", "batches"])
+@pytest.mark.parametrize("keys", list(KEYS))
 @pytest.mark.parametrize("dtype,d,Ch", [(torch.bfloat16, 128, 8), (torch.bfloat16, 64, 16),
                                         (torch.float32, 64, 2), (torch.bfloat16, 128, 0),
                                         (torch.float32, 128, 0)])
 def test_crowded_codes(dtype, d, Ch, keys, heads):
     from paper_2607_12789_amd import avq
-    M0 = 16
+    M0 = len(KEYS[keys])
     g = torch.Generator().manual_seed(7)
-    par = crowded(M0, GIANT if keys == "giant" else BATCHES, g).cuda()
+    par = crowded(M0, KEYS[keys], g).cuda()
     N = len(par)
     if heads * N * d >= 2 ** 30:
         heads = 128
@@ -90,7 +93,7 @@ def test_crowded_codes(dtype, d, Ch, keys, heads):
         check(V1, par, code, M0, Ch, packed[0, h], counts[0, h], Vbar[0, h])
 
 
-@pytest.mark.parametrize("keys", ["giant", "batches"])
+@pytest.mark.parametrize("keys", list(KEYS))
 @pytest.mark.parametrize("dtype,d,Ch", [(torch.bfloat16, 128, 8), (torch.bfloat16, 64, 4),
                                         (torch.bfloat16, 128, 16), (torch.float32, 64, 16),
                                         (torch.float32, 128, 8)])
@@ -98,9 +101,9 @@ def test_crowded_fused(dtype, d, Ch, keys):
     """The fused pass on the same crowds: the codes of avq_assign exactly, and
     the sums of those codes."""
     from paper_2607_12789_amd import avq
-    M0, heads = 16, 128
+    M0, heads = len(KEYS[keys]), 128
     g = torch.Generator().manual_seed(9)
-    par = crowded(M0, GIANT if keys == "giant" else BATCHES, g)
+    par = crowded(M0, KEYS[keys], g)
     N = len(par)
     Cp = torch.randn(M0, d, generator=g)
     Cc = Cp[:, None] + 0.1 * torch.randn(M0, Ch, d, generator=g)
