@@ -2,8 +2,8 @@
 // convention that a parent row covers its whole cell and a child row the keys
 // that moved to it; and the same pass with the child compare of Alg. 1 in it.
 //
-// A family is a parent and its Ch children (Ch = 0, a flat codebook: 16
-// consecutive parents). One workgroup owns one (batch, head) and a range of F
+// A family is a parent and its Ch children (Ch = 0, a flat codebook: 16, 8 or 4
+// consecutive parents, or fewer, see launch_aggregate_cfg). One workgroup owns one (batch, head) and a range of F
 // families and is the only writer of their rows, so there are no float
 // atomics and no partial results in HBM. The workgroup
 //   1. scans the head's codes once: every wave compacts the keys of the range
@@ -53,6 +53,7 @@
 #include "avq_packed.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace avq {
 
@@ -61,7 +62,8 @@ constexpr int kGroup = 32;        // keys per group
 
 enum AggMode {
   kAggCodes,  // codes given, Ch >= 1
-  kAggFlat,   // codes given, Ch = 0
+  kAggFlat,   // codes given, Ch = 0: families of 16 parents
+  kAggFlatFew,  // the same with fewer parents per family
   kAggFused,  // parent indices given; the child compare writes the codes
 };
 
@@ -78,7 +80,7 @@ struct FusedArgs {
 template <typename T, int D, int NT, int MODE, bool SMALL>
 struct AggCfg {
   static constexpr bool kB = Elem<T>::kBf16;
-  static constexpr bool kFlat = MODE == kAggFlat;
+  static constexpr bool kFlat = MODE == kAggFlat || MODE == kAggFlatFew;
   static constexpr bool kFused = MODE == kAggFused;
   // SMALL: 4 workgroups of 4 waves per CU, whose phases overlap, instead of
   // one of up to 16 waves (see launch_aggregate_nt). Otherwise as many waves
@@ -125,6 +127,26 @@ struct AggCfg {
                         4 * kGroup * kMaxFamilies <= kLds,
                 "a key list of one group per family fits the LDS");
 };
+
+// Families of a flat codebook, of 2^rsh parents each: whole octets, as many as
+// hold the M0 parents (the padding octets after them belong to none).
+constexpr int flat_families(int M0, int rsh) {
+  return rsh >= 3 ? (M0 + (1 << rsh) - 1) >> rsh : (M0 + 7) / 8 << (3 - rsh);
+}
+
+// log2 of the parents per family of a flat codebook: 16, as many as a product
+// has rows, or fewer where that leaves CUs without a workgroup and the keys
+// are more than a few; the most that give every one of `workgroups` a family.
+// Aggregation in us, 16 parents / the chosen number: bf16, 1 head x 256 parents,
+// N = 2^20, d = 128: 1000 / 222; 4 x 128, N = 65536: 57.3 / 31.0; 32 x 64, N = 8192,
+// d = 64: 20.8 / 14.0; 1 x 8, N = 65536, d = 64: 262 / 50; fp32, 4 x 128, N = 65536, d =
+// 128: 158.7 / 43.4; but 8 x 500, N = 300, d = 128: 6.0 / 6.4 (8 parents; 16 taken).
+constexpr int flat_shift(long long BH, int N, int M0, long long workgroups) {
+  int rsh = 4;
+  if (N > 512)
+    while (rsh > 0 && BH * flat_families(M0, rsh) < workgroups) --rsh;
+  return rsh;
+}
 
 // A value row piece of one lane: 16 bytes (bf16 at d = 64: 8), at the
 // lane's columns; column col(t, c) belongs to column tile t.
@@ -174,7 +196,7 @@ __attribute__((amdgpu_waves_per_eu(AggCfg<T, D, NT, MODE, SMALL>::kWaves *
 void aggregate_kernel(
     const T* __restrict__ V, const int32_t* __restrict__ code_idx, float* __restrict__ Vbar,
     int32_t* __restrict__ counts, unsigned char* __restrict__ packed, int N, int M0, int Ch,
-    int F, int ranges, int cap, FusedArgs fa) {
+    int F, int ranges, int cap, int rsh, FusedArgs fa) {
   using Cfg = AggCfg<T, D, NT, MODE, SMALL>;
   constexpr bool kB = Cfg::kB, kFlat = Cfg::kFlat, kFused = Cfg::kFused;
   constexpr int W = Cfg::kWaves, CT = Cfg::CT, ROWS = Cfg::ROWS;
@@ -189,7 +211,9 @@ void aggregate_kernel(
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int bh = blk / ranges;
   const PackedLayout PL = packed_layout(M0, Ch, D, (int)sizeof(T));
-  const int n_fam = kFlat ? PL.PO / 2 : M0;  // flat: the padding octets' families too
+  if constexpr (MODE != kAggFlatFew) rsh = 4;
+  const int R = 1 << rsh;  // flat: parents per family
+  const int n_fam = kFlat ? flat_families(M0, rsh) : M0;
   const int p0 = (blk % ranges) * F;
   const int nfam = min(F, n_fam - p0);
   const int Mtot = M0 * (1 + Ch);
@@ -206,8 +230,8 @@ void aggregate_kernel(
     if constexpr (kFused) {
       f = code - p0;
     } else if constexpr (kFlat) {
-      f = (code >> 4) - p0;
-      row = code & 15;
+      f = (code >> rsh) - p0;
+      row = code & (R - 1);
       if (code >= M0) f = -1;
     } else {
       const int x = code - M0;
@@ -409,7 +433,7 @@ void aggregate_kernel(
     for (int nt = 0; nt < NT; ++nt) {
       // the code of row x, or -1
       auto code_of = [&](int x) {
-        if constexpr (kFlat) return 16 * p + x < M0 ? 16 * p + x : -1;
+        if constexpr (kFlat) return x < R && R * p + x < M0 ? R * p + x : -1;
         return x < 8 ? (8 * nt + x < Ch ? M0 + p * Ch + 8 * nt + x : -1) : (x == 8 && nt == 0 ? p : -1);
       };
       float inv[4];
@@ -437,46 +461,68 @@ void aggregate_kernel(
       // rows 0..7 (flat: and 8..15) through the staging area, so that each
       // store is 16 consecutive bytes per lane over the whole octet. 16-byte
       // units are XOR-swizzled so that the lanes' columns hit distinct banks.
+      // (flat families of fewer than 8 parents: parts of an octet, stored as they
+      // lie)
       constexpr int kUnits = Cfg::OCT_BYTES / 16;  // per octet
       auto swz = [&](int u) { return u ^ ((u >> 3) & 7); };
-      const bool mine = kFlat || g < 2;
+      const bool part = MODE == kAggFlatFew && R < 8;
+      const bool mine = kFlat ? 4 * g < R : g < 2;  // rows of the octets
       const int oct = kFlat ? g / 2 : 0;  // octet of the staging area
+      const int o0 = kFlat ? R * p / 8 : PL.PO + p * PL.CO + nt;  // the family's first
+      const int q0 = part ? R * p % 8 : 4 * (g & 1);  // the lane's first slot in the octet
       if (mine) {
         unsigned char* so = st + oct * Cfg::OCT_BYTES;
 #pragma unroll
         for (int t = 0; t < CT; ++t) {
           const int col = VR::col(t, c);
-          if constexpr (kB) {
-            const bf16x4 o = {(bf16)(acc[nt][t][0] * inv[0]), (bf16)(acc[nt][t][1] * inv[1]),
-                              (bf16)(acc[nt][t][2] * inv[2]), (bf16)(acc[nt][t][3] * inv[3])};
-            *reinterpret_cast<bf16x4*>(so + 16 * swz(col) + 8 * (g & 1)) = o;
+          using V4 = typename std::conditional<kB, bf16x4, f32x4>::type;
+          const V4 o = {(T)(acc[nt][t][0] * inv[0]), (T)(acc[nt][t][1] * inv[1]),
+                        (T)(acc[nt][t][2] * inv[2]), (T)(acc[nt][t][3] * inv[3])};
+          if (part) {
+            T* dst = means + ((size_t)o0 * D + col) * 8 + q0;
+            if (R == 4) {
+              *reinterpret_cast<V4*>(dst) = o;
+            } else {
+              dst[0] = o[0];
+              if (R == 2) dst[1] = o[1];
+            }
+          } else if constexpr (kB) {
+            *reinterpret_cast<V4*>(so + 16 * swz(col) + 2 * q0) = o;
           } else {
-            const f32x4 o = {acc[nt][t][0] * inv[0], acc[nt][t][1] * inv[1],
-                             acc[nt][t][2] * inv[2], acc[nt][t][3] * inv[3]};
-            *reinterpret_cast<f32x4*>(so + 16 * swz(2 * col + (g & 1))) = o;
+            *reinterpret_cast<V4*>(so + 16 * swz(2 * col + q0 / 4)) = o;
           }
         }
         if (c == 0) {
-          const int o = kFlat ? 2 * p + oct : PL.PO + p * PL.CO + nt;
+          float* io = &info[(size_t)(o0 + oct) * 16 + q0];
           f32x4 n4, l4;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             n4[r] = an[nt][r];
             l4[r] = ln_n(an[nt][r]);
           }
-          *reinterpret_cast<f32x4*>(&info[(size_t)o * 16 + 4 * (g & 1)]) = n4;
-          *reinterpret_cast<f32x4*>(&info[(size_t)o * 16 + 8 + 4 * (g & 1)]) = l4;
+          if (!kFlat || R >= 4) {
+            *reinterpret_cast<f32x4*>(io) = n4;
+            *reinterpret_cast<f32x4*>(io + 8) = l4;
+          } else {
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+              if (r < R) {
+                io[r] = n4[r];
+                io[8 + r] = l4[r];
+              }
+          }
         }
       }
+      if (part) continue;
       wave_lds_fence();
       constexpr int kOcts = kFlat ? 2 : 1;
 #pragma unroll
       for (int i = 0; i < kOcts * kUnits / kWave; ++i) {
         const int u = lq + kWave * i;
-        const int o = kFlat ? 2 * p + u / kUnits : PL.PO + p * PL.CO + nt;
+        if (kFlat && u / kUnits * 8 >= R) break;  // wave-uniform
         const uint4 v = *reinterpret_cast<const uint4*>(st + (u / kUnits) * Cfg::OCT_BYTES + 16 * swz(u % kUnits));
-        *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(means) + (size_t)o * Cfg::OCT_BYTES +
-                                  16 * (u % kUnits)) = v;
+        *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(means) +
+                                  (size_t)(o0 + u / kUnits) * Cfg::OCT_BYTES + 16 * (u % kUnits)) = v;
       }
       wave_lds_fence();
     }
@@ -775,9 +821,17 @@ void aggregate_kernel(
     f0 = f1;
   }
 
-  // ---- parent octets (flat: written above) ---------------------------------
+  // ---- parent octets (flat: written above, but for the padding) ------------
   if (!pk) return;
-  if constexpr (!kFlat) {
+  if constexpr (kFlat) {
+    if (p0 + nfam == n_fam) {
+      const int o0 = n_fam * R / 8;
+      uint4* pad = reinterpret_cast<uint4*>(means + (size_t)o0 * D * 8);
+      for (int i = tid; i < (PL.PO - o0) * Cfg::OCT_BYTES / 16; i += Cfg::kThreads) pad[i] = uint4{0, 0, 0, 0};
+      for (int i = tid; i < (PL.PO - o0) * 16; i += Cfg::kThreads)
+        info[(size_t)o0 * 16 + i] = i % 16 < 8 ? 0.f : kNegInf;
+    }
+  } else {
     const int p_end = p0 + nfam >= M0 ? 8 * PL.PO : p0 + nfam;  // the last range: the padding too
     if (F % 8 == 0) {
       const int o0 = p0 / 8;
@@ -837,8 +891,14 @@ hipError_t launch_aggregate_cfg(int BH, int N, int M0, int Ch, const void* V,
   DeviceInfo dev;
   hipError_t e = device_info(&dev);
   if (e != hipSuccess) return e;
-  const int n_fam = Cfg::kFlat ? packed_layout(M0, Ch, D, (int)sizeof(T)).PO / 2 : M0;
   const long long cus = dev.cus > 1 ? dev.cus : 1;
+  const int rsh = Cfg::kFlat ? flat_shift(BH, N, M0, cus * std::min(Cfg::kPerCU, 2)) : 4;
+  if constexpr (MODE == kAggFlat) {
+    if (rsh < 4)
+      return launch_aggregate_cfg<T, D, NT, kAggFlatFew, SMALL>(BH, N, M0, Ch, V, code_idx, Vbar,
+                                                                counts, packed, fa, stream);
+  }
+  const int n_fam = Cfg::kFlat ? flat_families(M0, rsh) : M0;
   const int F = families_per_workgroup(BH, n_fam, cus * Cfg::kPerCU);
   const int ranges = (n_fam + F - 1) / F;
   const long long grid = (long long)BH * ranges;
@@ -850,13 +910,13 @@ hipError_t launch_aggregate_cfg(int BH, int N, int M0, int Ch, const void* V,
   const int cap = (int)std::min<long long>(room, most);
   if (cap < F * kGroup) return hipErrorInvalidConfiguration;
   const int lds = Cfg::off_list(F) + 4 * cap;
-  constexpr int slot = 64 + ((((Elem<T>::kBf16 ? 0 : 1) * 2 + (D == 128 ? 1 : 0)) * 2 + (NT - 1)) * 3 + MODE) +
+  constexpr int slot = 64 + ((((Elem<T>::kBf16 ? 0 : 1) * 2 + (D == 128 ? 1 : 0)) * 2 + (NT - 1)) * 4 + MODE) +
                        (SMALL ? 64 : 0);
   e = ensure_dynamic_lds((const void*)aggregate_kernel<T, D, NT, MODE, SMALL>, lds, slot);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((aggregate_kernel<T, D, NT, MODE, SMALL>), dim3((unsigned)grid),
                      dim3(Cfg::kThreads), lds, stream, static_cast<const T*>(V), code_idx, Vbar,
-                     counts, static_cast<unsigned char*>(packed), N, M0, Ch, F, ranges, cap, fa);
+                     counts, static_cast<unsigned char*>(packed), N, M0, Ch, F, ranges, cap, rsh, fa);
   return hipGetLastError();
 }
 

@@ -1,0 +1,42 @@
+"""How the aggregation divides a head among workgroups (compile time, no GPU
+needed): a flat codebook's families hold fewer parents where 16 of them would
+leave compute units idle, and still cover every parent in whole octets.
+"""
+import subprocess
+
+from paper_2607_12789_amd import build
+
+CHECK = """
+#include "avq_aggregate.hip"
+namespace avq {
+constexpr bool covers() {
+  for (int M0 = 1; M0 <= 512; ++M0)
+    for (int rsh = 0; rsh <= 4; ++rsh) {
+      const int parents = flat_families(M0, rsh) << rsh;
+      const int octets = (M0 + 63) / 64 * 8;  // as packed_layout
+      if (parents < M0 || parents % 8 != 0 || parents > 8 * octets) return false;
+    }
+  return true;
+}
+static_assert(covers(), "whole octets, every parent, none past the padding");
+// workgroups of (heads, N, M0): enough for every slot, while the parents last
+constexpr long long families(long long BH, int N, int M0, long long slots) {
+  return BH * flat_families(M0, flat_shift(BH, N, M0, slots));
+}
+static_assert(families(1, 1 << 20, 256, 256) == 256);
+static_assert(families(4, 65536, 128, 256) == 256);
+static_assert(families(1, 65536, 8, 256) == 8);
+static_assert(families(32, 8192, 64, 512) == 512);
+static_assert(flat_shift(48, 16384, 512, 256) == 4);
+static_assert(flat_shift(1, 512, 512, 256) == 4);  // few keys: 16 parents
+}
+"""
+
+
+def test_flat_families(tmp_path):
+    src = tmp_path / "check.hip"
+    src.write_text(CHECK)
+    r = subprocess.run([build.HIPCC, "--offload-arch=gfx950", "-std=c++17", "--cuda-host-only",
+                        "-fsyntax-only", "-fconstexpr-steps=10000000", f"-I{build.CSRC}",
+                        str(src)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr

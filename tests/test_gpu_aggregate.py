@@ -137,3 +137,23 @@ def test_long_head(N):
     packed, counts, Vbar = avq.aggregate(V.view(1, 1, N, d), code.to(torch.int32).view(1, 1, N),
                                          M0, Ch, sums=True)
     check(V, par, code, M0, Ch, packed[0, 0], counts[0, 0], Vbar[0, 0])
+
+
+@pytest.mark.parametrize("heads", [1, 13, 26, 52, 103, 171])
+@pytest.mark.parametrize("M0", [37, 100])
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 64), (torch.bfloat16, 128),
+                                     (torch.float32, 64), (torch.float32, 128)])
+def test_flat_families(dtype, d, M0, heads):
+    """Flat codebooks with 1, 2, 4, 8 and 16 parents per family: at M0 = 37 the
+    number of heads at which a 256-CU device goes from one to the next; the
+    last family and octet are partly padding."""
+    from paper_2607_12789_amd import avq
+    N = 1100
+    g = torch.Generator(device="cuda").manual_seed(13)
+    # a skewed head: the last parent empty, one parent with a quarter of the keys
+    code = torch.randint(0, M0 - 1, (heads, N), device="cuda", generator=g)
+    code[:, ::4] = 7
+    V = torch.randn(heads, N, d, device="cuda", generator=g).to(dtype)
+    packed, counts, Vbar = avq.aggregate(V[None], code[None].to(torch.int32), M0, 0, sums=True)
+    for h in sorted({0, heads // 2, heads - 1}):
+        check(V[h], code[h], code[h], M0, 0, packed[0, h], counts[0, h], Vbar[0, h])
