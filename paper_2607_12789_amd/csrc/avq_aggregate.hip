@@ -82,12 +82,13 @@ struct AggCfg {
   static constexpr bool kB = Elem<T>::kBf16;
   static constexpr bool kFlat = MODE == kAggFlat || MODE == kAggFlatFew;
   static constexpr bool kFused = MODE == kAggFused;
-  // SMALL: 4 workgroups of 4 waves per CU, whose phases overlap, instead of
-  // one of up to 16 waves (see launch_aggregate_nt). Otherwise as many waves
+  // SMALL: 4 workgroups of 4 waves per CU (2 where the registers or the LDS
+  // hold no more), whose phases overlap, instead of one of up to 16 waves (see
+  // kSmallKeys). Otherwise as many waves
   // as the registers (16: 128 per lane, 12: 168, 8: 256) and the LDS (flat at
   // d = 128: 8) allow; the fused bf16 pass at d = 128 spills with 168
   // registers and is faster with 8 waves (c4 precompute 104 -> 96 us).
-  static constexpr int kPerCU = SMALL ? 4 : 1;
+  static constexpr int kPerCU = SMALL ? (kB && D == 64 ? 4 : 2) : 1;
   static constexpr int kWaves =
       SMALL      ? 4
       : D == 128 ? (kFlat || kFused || NT == 2 ? 8 : kB ? 16 : 12)
@@ -920,21 +921,29 @@ hipError_t launch_aggregate_cfg(int BH, int N, int M0, int Ch, const void* V,
   return hipGetLastError();
 }
 
-// bf16 at d = 64 with Ch <= 8, below 16384 keys per head: SMALL. Their rows
-// stream for a few us only, so a workgroup's chain of phases sets the time
-// unless several workgroups per CU overlap theirs; with more keys the scan of
-// all codes by four times as many workgroups costs what that gains.
-// Precompute, SMALL / one 16-wave workgroup per CU, us: 96 heads x 256
-// families, N = 4096: 57.7 / 71.9; 48 x 256, N = 2048: 29.0 / 36.4; 48 x 64,
-// N = 16384: 63.7 / 64.9; 16 x 256, N = 16384: 39.2 / 38.2; 4 x 128,
-// N = 65536: 47.7 / 39.0. (At d = 128 two workgroups of 4 waves per CU are no
-// faster than one of 8: 64 x 128, N = 4096: 52.4 / 52.7.)
+// Ch <= 8 with few keys per head: SMALL. Their rows stream for a few us only,
+// so a workgroup's chain of phases sets the time unless several workgroups
+// per CU overlap theirs; with more keys the scan of all codes by more
+// workgroups costs what that gains. bf16 at d = 64 (4 workgroups per CU) below
+// 16384 keys. Precompute, SMALL / one 16-wave workgroup per CU, us: 96 heads x
+// 256 families, N = 4096: 57.7 / 71.9; 48 x 256, N = 2048: 29.0 / 36.4; 48 x 64,
+// N = 16384: 63.7 / 64.9; 16 x 256, N = 16384: 39.2 / 38.2; 4 x 128, N = 65536:
+// 47.7 / 39.0. The others (2 per CU) below 1024. Aggregation, SMALL / one per
+// CU, us: bf16, d = 128, 300 heads x 100 families, N = 512: 46.6 / 66.2; 48 x 64,
+// N = 1024: 0.99 to 1.10 of one per CU's time; 16 x 256, N = 16384: 1.13; 64 x
+// 128, N = 4096 (precompute): 52.4 / 52.7; fp32, d = 64, 1000 x 16, N = 130: 0.57;
+// 300 x 100, N = 512: 38.0 / 65.5. (fp32 flat codebooks of
+// 8192 keys gain 3 to 10%, but lose up to 1.9 times where one family holds most of
+// the keys: 4 waves' fp32 products.)
+template <typename T, int D>
+constexpr int kSmallKeys = Elem<T>::kBf16 && D == 64 ? 16384 : 1024;
+
 template <typename T, int D, int NT, int MODE>
 hipError_t launch_aggregate_nt(int BH, int N, int M0, int Ch, const void* V,
                                const int32_t* code_idx, float* Vbar, int32_t* counts,
                                void* packed, const FusedArgs& fa, hipStream_t stream) {
-  if constexpr (Elem<T>::kBf16 && D == 64 && NT == 1) {
-    if (N < 16384)
+  if constexpr (NT == 1) {
+    if (N < kSmallKeys<T, D>)
       return launch_aggregate_cfg<T, D, NT, MODE, true>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
                                                         packed, fa, stream);
   }

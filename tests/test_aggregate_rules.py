@@ -1,6 +1,7 @@
 """How the aggregation divides a head among workgroups (compile time, no GPU
 needed): a flat codebook's families hold fewer parents where 16 of them would
-leave compute units idle, and still cover every parent in whole octets.
+leave compute units idle, and still cover every parent in whole octets; heads
+of few keys take the small workgroups, several per compute unit.
 """
 import subprocess
 
@@ -29,6 +30,12 @@ static_assert(families(1, 65536, 8, 256) == 8);
 static_assert(families(32, 8192, 64, 512) == 512);
 static_assert(flat_shift(48, 16384, 512, 256) == 4);
 static_assert(flat_shift(1, 512, 512, 256) == 4);  // few keys: 16 parents
+// heads of few keys share a compute unit with others, whatever the type
+static_assert(kSmallKeys<bf16, 64> > 4096 && kSmallKeys<bf16, 128> > 512 &&
+              kSmallKeys<float, 64> > 512 && kSmallKeys<float, 128> > 512);
+// heads of many keys do not
+static_assert(kSmallKeys<bf16, 64> <= 16384 && kSmallKeys<bf16, 128> <= 4096 &&
+              kSmallKeys<float, 64> <= 4096 && kSmallKeys<float, 128> <= 4096);
 }
 """
 

@@ -123,6 +123,92 @@ def test_crowded_fused(dtype, d, Ch, keys):
               Vbar[0, h])
 
 
+# a head of at most 12000 keys: one family past the list of a small workgroup
+# (about 6000 keys), and 16 or 64 families that are past it together
+SMALL_GIANT = [31, 32, 33, 0, 1, 11000, 0, 64, 65, 5, 0, 0, 17, 96, 2, 0]
+SMALL_BATCHES = {16: [740 + 7 * (p % 3) for p in range(16)],
+                 64: [180 + 7 * (p % 3) for p in range(64)]}
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("keys", ["giant", "batches"])
+@pytest.mark.parametrize("Ch", [0, 4, 8])
+def test_crowded_small_workgroups(Ch, keys, fused):
+    """The same crowds in the small workgroups, whose lists are the shortest
+    (bf16, d = 64, below 16384 keys), with so many heads that a workgroup holds
+    all the families."""
+    from paper_2607_12789_amd import avq
+    dtype, d, heads = torch.bfloat16, 64, 1024
+    per = SMALL_GIANT if keys == "giant" else SMALL_BATCHES[16 if Ch else 64]
+    M0 = len(per)
+    g = torch.Generator().manual_seed(17)
+    par = crowded(M0, per, g)
+    N = len(par)
+    assert 6500 < N < 16384
+    V1 = torch.randn(N, d, generator=g).to(dtype).cuda()
+    V = V1.expand(1, heads, N, d).contiguous()
+    if fused:
+        Cp = torch.randn(M0, d, generator=g)
+        Cc = Cp[:, None] + 0.1 * torch.randn(M0, Ch, d, generator=g)
+        pick = torch.randint(0, Ch + 1, (N,), generator=g)
+        rows = torch.cat([Cp[:, None], Cc], 1)[par, pick]
+        K1 = (rows + 0.05 * torch.randn(N, d, generator=g)).to(dtype).cuda()
+        K = K1.expand(1, heads, N, d).contiguous()
+        cp = Cp.to(dtype).cuda().expand(heads, M0, d).contiguous()
+        cc = Cc.to(dtype).cuda().expand(heads, M0, Ch, d).contiguous()
+        p_idx, c_idx, packed, counts, Vbar = avq.assign_aggregate(K, V, cp, cc, sums=True)
+        p_ref, c_ref = avq.assign(K[:, :2].contiguous(), cp[:2].contiguous(), cc[:2].contiguous())
+        assert torch.equal(p_idx[:, :2], p_ref) and torch.equal(c_idx[:, :2], c_ref)
+        assert (c_idx == c_idx[:, :1]).all()
+        par, code = p_idx[0, 0].long(), c_idx[0, 0].long()
+    else:
+        child = torch.randint(-1, max(Ch, 1), (N,), generator=g)
+        code = (torch.where(child < 0, par, M0 + par * Ch + child) if Ch else par).cuda()
+        par = par.cuda()
+        codes = code.to(torch.int32).expand(1, heads, N).contiguous()
+        packed, counts, Vbar = avq.aggregate(V, codes, M0, Ch, sums=True)
+    for h in (0, heads // 2, heads - 1):
+        check(V1, par, code, M0, Ch, packed[0, h], counts[0, h], Vbar[0, h])
+
+
+@pytest.mark.parametrize("dtype,d,Ch", [(torch.bfloat16, 128, 0), (torch.bfloat16, 128, 4),
+                                        (torch.float32, 64, 8), (torch.float32, 128, 0),
+                                        (torch.float32, 128, 8)])
+@pytest.mark.parametrize("N,M0,heads", [(1, 3, 5), (130, 16, 600), (1023, 100, 300),
+                                        (1023, 512, 3)])
+def test_short_heads(dtype, d, Ch, N, M0, heads):
+    """Heads of fewer than 1024 keys: the small workgroups, two per compute
+    unit, of the other types and widths; codes and (Ch >= 1) the fused pass."""
+    from paper_2607_12789_amd import avq
+    g = torch.Generator(device="cuda").manual_seed(19)
+
+    def randn(*s):
+        return torch.randn(*s, device="cuda", generator=g)
+
+    par = torch.randint(0, M0, (heads, N), device="cuda", generator=g)
+    V = randn(heads, N, d).to(dtype)
+    if Ch == 0:
+        packed, counts, Vbar = avq.aggregate(V[None], par[None].to(torch.int32), M0, 0, sums=True)
+        for h in sorted({0, heads // 2, heads - 1}):
+            check(V[h], par[h], par[h], M0, 0, packed[0, h], counts[0, h], Vbar[0, h])
+        return
+    Cp = randn(heads, M0, d)
+    Cc = Cp[:, :, None] + 0.1 * randn(heads, M0, Ch, d)
+    pick = torch.randint(0, Ch, (heads, N), device="cuda", generator=g)
+    hh = torch.arange(heads, device="cuda")[:, None]
+    K = (Cc[hh, par, pick] + 0.05 * randn(heads, N, d)).to(dtype)[None]
+    cp, cc = Cp.to(dtype), Cc.to(dtype)
+    p_idx, c_idx, packed, counts, Vbar = avq.assign_aggregate(K, V[None], cp, cc, sums=True)
+    p_ref, c_ref = avq.assign(K, cp, cc)
+    assert torch.equal(p_idx, p_ref) and torch.equal(c_idx, c_ref)
+    packed2, counts2, Vbar2 = avq.aggregate(V[None], c_idx, M0, Ch, sums=True)
+    assert torch.equal(counts, counts2)
+    for h in sorted({0, heads // 2, heads - 1}):
+        p, c = p_idx[0, h].long(), c_idx[0, h].long()
+        check(V[h], p, c, M0, Ch, packed[0, h], counts[0, h], Vbar[0, h])
+        check(V[h], p, c, M0, Ch, packed2[0, h], counts2[0, h], Vbar2[0, h])
+
+
 @pytest.mark.parametrize("N", [2 ** 21 - 3, 2 ** 21 + 5])
 def test_long_head(N):
     """More keys than a compacted entry's key field holds (2^21), and the

@@ -29,14 +29,12 @@ template <typename T, int D>
 constexpr bool all_ok() {
   return layout_ok<T, D, 1, kAggCodes, false>() && layout_ok<T, D, 2, kAggCodes, false>() &&
          layout_ok<T, D, 1, kAggFlat, false>() && layout_ok<T, D, 1, kAggFlatFew, false>() &&
-         layout_ok<T, D, 1, kAggFused, false>() && layout_ok<T, D, 2, kAggFused, false>();
+         layout_ok<T, D, 1, kAggFused, false>() && layout_ok<T, D, 2, kAggFused, false>() &&
+         layout_ok<T, D, 1, kAggCodes, true>() && layout_ok<T, D, 1, kAggFlat, true>() &&
+         layout_ok<T, D, 1, kAggFlatFew, true>() && layout_ok<T, D, 1, kAggFused, true>();
 }
 static_assert(all_ok<bf16, 64>() && all_ok<bf16, 128>() && all_ok<float, 64>() &&
                   all_ok<float, 128>(), "key list");
-static_assert(layout_ok<bf16, 64, 1, kAggCodes, true>() &&
-                  layout_ok<bf16, 64, 1, kAggFlat, true>() &&
-                  layout_ok<bf16, 64, 1, kAggFlatFew, true>() &&
-                  layout_ok<bf16, 64, 1, kAggFused, true>(), "key list");
 }
 """
 
