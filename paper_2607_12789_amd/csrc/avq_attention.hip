@@ -1228,15 +1228,36 @@ hipError_t launch_attention_cfg(const AttnArgs& a, int BH, hipStream_t stream) {
 // 65.2; d = 128 always (P = 85 107.1 / 94.9; M0 = 64, P = 64, 1000 tiles 39.6 /
 // 33.8). (Half octets in the pair's path cost its other Ch 3 to 11%.)
 //
+// A pair's tiles are of one head, so a head with an odd number of tiles leaves
+// half a pair idle: one tile per head is never paired (334 heads of 4 queries,
+// M0 = P = 512, Ch = 16: 274 us single, 349 paired), and an odd number only where
+// the idle halves cost less than the pairs gain, which for few tiles per head
+// is where the workgroups run in fewer rounds. One / two tiles in us, M0 = 256,
+// Ch = 8, P = 128, blocks of 32: 3 tiles per head, d = 64, 300 heads (2 rounds,
+// pairs 1) 72.3 / 52.9, 512 (2, 2) 64.8 / 88.3, d = 128, 512 (3, 2) 125.0 /
+// 138.7; 5, d = 64, 300 (2, 2) 90.0 / 93.8, 512 (4, 2) 0.94 of one tile's time.
+// Blocks of 64: 3, d = 64, 512 (2, 2) 0.99 to 1.09; 5, 300 (2, 2) 0.93 to 1.03;
+// d = 128 always (300, 2, 2: 0.92 to 0.99).
+//
 // fp32: only for blocks of 32, once tiles outnumber two per CU (8 heads x 4096
 // queries x 64: 121 us with one tile of 32-query waves, 56 now; with Ch = 4, P =
 // 170 of 256, 1200 tiles 296 / 230).
 template <typename T, int D>
-constexpr bool pair_tiles(int block_q, long long tiles, long long cus, int M0, int Ch, int P) {
+constexpr bool pair_tiles(int block_q, int n_tiles, long long BH, long long cus, int M0, int Ch,
+                          int P) {
+  if (n_tiles < 2) return false;
+  const long long tiles = BH * n_tiles;
   if (!Elem<T>::kBf16) return block_q <= 32 && tiles > 2 * cus;
   if (block_q > 64) return false;
   const long long round = AttnCfg<T, D, 4, 1, 32>::kWavesPerEu * cus;  // workgroups at once
   if (tiles <= round && (block_q <= 32 || tiles <= cus || tiles > 2 * cus)) return false;
+  if (n_tiles % 2 != 0) {
+    const long long pairs = BH * ((n_tiles + 1) / 2);
+    const bool no_fewer = (pairs + round - 1) / round >= (tiles + round - 1) / round;
+    if (block_q <= 32 ? (n_tiles == 3 ? pairs > round : no_fewer)
+                      : (n_tiles == 3 && D == 64 && no_fewer))
+      return false;
+  }
   if (Ch != 2 && Ch != 4) return true;
   int share;
   if (tiles <= round) share = 10;
@@ -1250,8 +1271,8 @@ hipError_t launch_attention_tiles(const AttnArgs& a, int BH, hipStream_t stream)
   DeviceInfo dev;
   const hipError_t e = device_info(&dev);
   if (e != hipSuccess) return e;
-  const long long cus = dev.cus > 1 ? dev.cus : 1, tiles = (long long)BH * a.n_tiles;
-  const bool pair = pair_tiles<T, D>(a.block_q, tiles, cus, a.M0, a.Ch, a.P);
+  const long long cus = dev.cus > 1 ? dev.cus : 1;
+  const bool pair = pair_tiles<T, D>(a.block_q, a.n_tiles, BH, cus, a.M0, a.Ch, a.P);
   if constexpr (Elem<T>::kBf16) {
     if (pair && a.block_q <= 32) return launch_attention_cfg<T, D, 2, 2, 32, TILED>(a, BH, stream);
     if (pair) return launch_attention_cfg<T, D, 4, 2, 32, TILED>(a, BH, stream);
