@@ -529,15 +529,64 @@ void aggregate_kernel(
     }
   };
 
+  // writes family f without keys: zeros alone, so no group's chain of loads,
+  // products and stages is spent on it. Heads of few keys are mostly such
+  // families. Aggregation or fused pass with it in us, a group of padding for
+  // each / so: bf16, d = 128, 375 heads x 256 families, N = 25: 196 / 100; 147 x
+  // 512, Ch = 16, N = 181: 397 / 283; 95 x 512, Ch = 8, N = 403: 175 / 135; fp32, d
+  // = 128, 475 x 256, N = 1: 534 / 234.
+  auto write_empty = [&](int f) {
+    const int lane = hidden(tid % kWave), p = p0 + f;
+    const uint32_t z = hidden(0);
+    // n16 16-byte units of zeros
+    auto zeros = [&](void* dst, int n16) {
+      for (int i = lane; i < n16; i += kWave) static_cast<uint4*>(dst)[i] = uint4{z, z, z, z};
+    };
+    // rows of sums and counts: the parent and its children (flat: R parents)
+    auto rows = [&](int code, int n) {
+      if (lane < n) nb[code + lane] = z;
+      if (vb) zeros(vb + (size_t)code * D, n * D / 4);
+    };
+    if constexpr (kFlat) {
+      rows(R * p, min(R, M0 - R * p));
+    } else {
+      rows(p, 1);
+      rows(M0 + p * Ch, Ch);
+    }
+    if (!pk) return;
+    // n slots of octet o from slot q0 on, or (n a multiple of 8) whole octets
+    auto slots = [&](int o, int q0, int n) {
+      if (n % 8 == 0) {
+        zeros(means + (size_t)o * D * 8, n / 8 * Cfg::OCT_BYTES / 16);
+      } else {
+        for (int i = lane; i < D * n; i += kWave)
+          means[((size_t)o * D + i / n) * 8 + q0 + i % n] = T(__uint_as_float(z));
+      }
+      if (lane < n) {
+        float* io = &info[(size_t)(o + lane / 8) * 16 + q0 + lane % 8];
+        io[0] = __uint_as_float(z);
+        io[8] = kNegInf;
+      }
+    };
+    if constexpr (kFlat) {
+      slots(R * p / 8, R * p % 8, R);
+    } else {
+      slots(PL.PO + p * PL.CO, 0, 8 * PL.CO);
+      for (int i = lane; i < D; i += kWave) pmean[f * D + i] = T(__uint_as_float(z));
+      if (lane == 0) L.cell[f] = __uint_as_float(z);
+    }
+  };
+
   // ---- 2. and 3. in batches of families that fit the key list ------------
   for (int f0 = 0; f0 < nfam;) {
-    // families f0 .. f1 - 1: each at least one group, so that the wave of its
-    // first group writes it, empty or not. Every wave finds the same plan.
+    // families f0 .. f1 - 1, groups for those with keys. Every wave finds the
+    // same plan.
     int f1;
     bool giant;
+    unsigned long long empty;  // families without keys
     {
       const int n = lane >= f0 && lane < nfam ? L.hist[lane] : 0;
-      const int ng = lane >= f0 && lane < nfam ? max(1, (n + kGroup - 1) / kGroup) : 0;
+      const int ng = (n + kGroup - 1) / kGroup;
       const int incl = wave_incl_scan(ng);
       if (lane < nfam) L.gstart[lane] = incl - ng;
       if (lane == nfam - 1) L.gstart[nfam] = incl;
@@ -545,6 +594,7 @@ void aggregate_kernel(
       f1 = f0 + max(1, fit);
       // a family past the list: segments of the head that fit whatever they hold
       giant = fit == 0;
+      empty = __ballot(lane >= f0 && lane < f1 && n == 0);
     }
     wave_lds_fence();
     const bool from_priv = !spilled && f1 == nfam && f0 == 0 && !giant;
@@ -570,6 +620,10 @@ void aggregate_kernel(
         });
       }
       __syncthreads();
+      // the families without keys, in turn (past the barrier: their means lie where
+      // the private lists were)
+      for (int i = 0; empty; ++i, empty &= empty - 1)
+        if (i % W == wave) write_empty(__builtin_ctzll(empty));
       const int seg_n = L.cursor[f0];  // giant: keys of this segment
       const int NG = giant ? (seg_n + kGroup - 1) / kGroup : L.gstart[f1];
       const int gb = (int)((long long)NG * wave / W), ge = (int)((long long)NG * (wave + 1) / W);
@@ -592,7 +646,7 @@ void aggregate_kernel(
           return min(kGroup, tot - kGroup * (it - (giant ? 0 : L.gstart[ff])));
         };
         // list entries of group it (n keys): slots past n repeat the group's
-        // first key (an empty group: key 0)
+        // first key (no group: key 0)
         auto read_entries = [&](int it, int nk) {
           const uint4* q = reinterpret_cast<const uint4*>(&list[it * kGroup + 8 * g]);
           const uint4 a = q[0], b = q[1];
@@ -652,8 +706,12 @@ void aggregate_kernel(
 
         for (int it = gb; it < ge; ++it) {
           const bool last = !giant && L.gstart[f + 1] == it + 1;  // of the family
-          const int fn = last ? f + 1 : f;
           const bool more = it + 1 < ge;
+          int fn = f;  // the next group's family
+          if (last) {
+            do ++fn;
+            while (more && L.gstart[fn + 1] == it + 1);  // past those without keys
+          }
           // the 32 keys' row bits, two per word: bit x is accumulator row x
           uint32_t oh[NT][4];
           uint32_t kcur[2] = {0, 0};
@@ -721,8 +779,8 @@ void aggregate_kernel(
               }
             }
           }
-          // sums^T += onehot . V (an empty family's only group: nothing)
-          if (n > 0) {
+          // sums^T += onehot . V
+          {
             // the one-hot rows as a bf16 operand; their product with ones is the
             // counts (exact, and for fp32 one product instead of eight)
             bf16x8 a[NT];

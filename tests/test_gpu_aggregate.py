@@ -209,6 +209,15 @@ def test_short_heads(dtype, d, Ch, N, M0, heads):
         check(V[h], p, c, M0, Ch, packed2[0, h], counts2[0, h], Vbar2[0, h])
 
 
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 64), (torch.bfloat16, 128),
+                                     (torch.float32, 64), (torch.float32, 128)])
+@pytest.mark.parametrize("Ch", [0, 1, 8, 16])
+@pytest.mark.parametrize("N,M0,heads", [(1, 200, 70), (70, 203, 300)])
+def test_fewer_keys_than_codes(dtype, d, Ch, N, M0, heads):
+    """Most families have no keys: before, between and after those that do."""
+    test_short_heads(dtype, d, Ch, N, M0, heads)
+
+
 @pytest.mark.parametrize("N", [2 ** 21 - 3, 2 ** 21 + 5])
 def test_long_head(N):
     """More keys than a compacted entry's key field holds (2^21), and the
