@@ -529,61 +529,13 @@ void aggregate_kernel(
     }
   };
 
-  // writes family f without keys: zeros alone, so no group's chain of loads,
-  // products and stages is spent on it. Heads of few keys are mostly such
-  // families. Aggregation or fused pass with it in us, a group of padding for
-  // each / so: bf16, d = 128, 375 heads x 256 families, N = 25: 196 / 100; 147 x
-  // 512, Ch = 16, N = 181: 397 / 283; 95 x 512, Ch = 8, N = 403: 175 / 135; fp32, d
-  // = 128, 475 x 256, N = 1: 534 / 234.
-  auto write_empty = [&](int f) {
-    const int lane = hidden(tid % kWave), p = p0 + f;
-    const uint32_t z = hidden(0);
-    // n16 16-byte units of zeros
-    auto zeros = [&](void* dst, int n16) {
-      for (int i = lane; i < n16; i += kWave) static_cast<uint4*>(dst)[i] = uint4{z, z, z, z};
-    };
-    // rows of sums and counts: the parent and its children (flat: R parents)
-    auto rows = [&](int code, int n) {
-      if (lane < n) nb[code + lane] = z;
-      if (vb) zeros(vb + (size_t)code * D, n * D / 4);
-    };
-    if constexpr (kFlat) {
-      rows(R * p, min(R, M0 - R * p));
-    } else {
-      rows(p, 1);
-      rows(M0 + p * Ch, Ch);
-    }
-    if (!pk) return;
-    // n slots of octet o from slot q0 on, or (n a multiple of 8) whole octets
-    auto slots = [&](int o, int q0, int n) {
-      if (n % 8 == 0) {
-        zeros(means + (size_t)o * D * 8, n / 8 * Cfg::OCT_BYTES / 16);
-      } else {
-        for (int i = lane; i < D * n; i += kWave)
-          means[((size_t)o * D + i / n) * 8 + q0 + i % n] = T(__uint_as_float(z));
-      }
-      if (lane < n) {
-        float* io = &info[(size_t)(o + lane / 8) * 16 + q0 + lane % 8];
-        io[0] = __uint_as_float(z);
-        io[8] = kNegInf;
-      }
-    };
-    if constexpr (kFlat) {
-      slots(R * p / 8, R * p % 8, R);
-    } else {
-      slots(PL.PO + p * PL.CO, 0, 8 * PL.CO);
-      for (int i = lane; i < D; i += kWave) pmean[f * D + i] = T(__uint_as_float(z));
-      if (lane == 0) L.cell[f] = __uint_as_float(z);
-    }
-  };
-
   // ---- 2. and 3. in batches of families that fit the key list ------------
   for (int f0 = 0; f0 < nfam;) {
     // families f0 .. f1 - 1, groups for those with keys. Every wave finds the
     // same plan.
     int f1;
     bool giant;
-    unsigned long long empty;  // families without keys
+    unsigned long long filled;  // families with keys
     {
       const int n = lane >= f0 && lane < nfam ? L.hist[lane] : 0;
       const int ng = (n + kGroup - 1) / kGroup;
@@ -594,9 +546,13 @@ void aggregate_kernel(
       f1 = f0 + max(1, fit);
       // a family past the list: segments of the head that fit whatever they hold
       giant = fit == 0;
-      empty = __ballot(lane >= f0 && lane < f1 && n == 0);
+      filled = __ballot(lane >= f0 && lane < f1 && n > 0);
     }
     wave_lds_fence();
+    // the family of group x (one of families f0 .. f1 - 1), the same in every lane
+    auto family_of = [&](int x) {
+      return (int)__builtin_ctzll(__ballot(lane >= f0 && lane < f1 && L.gstart[lane + 1] > x));
+    };
     const bool from_priv = !spilled && f1 == nfam && f0 == 0 && !giant;
     zero_acc();
     for (int s0 = 0; s0 < N; s0 += giant ? cap : N) {
@@ -620,10 +576,6 @@ void aggregate_kernel(
         });
       }
       __syncthreads();
-      // the families without keys, in turn (past the barrier: their means lie where
-      // the private lists were)
-      for (int i = 0; empty; ++i, empty &= empty - 1)
-        if (i % W == wave) write_empty(__builtin_ctzll(empty));
       const int seg_n = L.cursor[f0];  // giant: keys of this segment
       const int NG = giant ? (seg_n + kGroup - 1) / kGroup : L.gstart[f1];
       const int gb = (int)((long long)NG * wave / W), ge = (int)((long long)NG * (wave + 1) / W);
@@ -638,8 +590,7 @@ void aggregate_kernel(
         VR vr[8];
         uint32_t ent[8];    // list entries 8 g .. 8 g + 7 (key, row)
         uint32_t kent[2];   // FUSED: entries of compare columns c
-        int f = f0;
-        while (!giant && L.gstart[f + 1] <= gb) ++f;  // wave-uniform
+        int f = giant ? f0 : family_of(gb);
         int n = 0;  // keys of the current group
         auto group_n = [&](int ff, int it) {
           const int tot = giant ? seg_n : L.hist[ff];
@@ -707,11 +658,8 @@ void aggregate_kernel(
         for (int it = gb; it < ge; ++it) {
           const bool last = !giant && L.gstart[f + 1] == it + 1;  // of the family
           const bool more = it + 1 < ge;
-          int fn = f;  // the next group's family
-          if (last) {
-            do ++fn;
-            while (more && L.gstart[fn + 1] == it + 1);  // past those without keys
-          }
+          // the next group's family, past those without keys
+          const int fn = !last ? f : more ? __builtin_ctzll(filled & (~1ull << f)) : f1;
           // the 32 keys' row bits, two per word: bit x is accumulator row x
           uint32_t oh[NT][4];
           uint32_t kcur[2] = {0, 0};
@@ -779,8 +727,10 @@ void aggregate_kernel(
               }
             }
           }
-          // sums^T += onehot . V
-          {
+          // sums^T += onehot . V. Every group has keys; the branch keeps the block
+          // apart (without it the compiler takes 4 registers more, spilled in the
+          // fp32 pass at d = 128)
+          if (n > 0) {
             // the one-hot rows as a bf16 operand; their product with ones is the
             // counts (exact, and for fp32 one product instead of eight)
             bf16x8 a[NT];
@@ -864,8 +814,7 @@ void aggregate_kernel(
       auto run_end = [&](int w) { return (int)((long long)NG * (w + 1) / W); };
       const int gb = (int)((long long)NG * wave / W), ge = run_end(wave);
       if (gb < ge) {
-        int f = f0;
-        while (L.gstart[f + 1] < ge) ++f;  // the family of the run's last group
+        const int f = family_of(ge - 1);
         if (L.gstart[f + 1] > ge && L.gstart[f] >= gb) {
           for (int w = wave + 1; w < W; ++w) {
             if (run_end(w) > run_end(w - 1)) add_slot(w);
@@ -878,6 +827,63 @@ void aggregate_kernel(
       __syncthreads();
     }
     f0 = f1;
+  }
+
+  // ---- families without keys ------------------------------------------------
+  // writes family f without keys: zeros alone, so no group's chain of loads,
+  // products and stages is spent on it. Heads of few keys are mostly such
+  // families. Aggregation or fused pass with it in us, a group of padding for
+  // each / so: bf16, d = 128, 375 heads x 256 families, N = 25: 196 / 100; 147 x
+  // 512, Ch = 16, N = 181: 397 / 283; 95 x 512, Ch = 8, N = 403: 175 / 135; fp32, d
+  // = 128, 475 x 256, N = 1: 534 / 234.
+  auto write_empty = [&](int f) {
+    const int lane = hidden(tid % kWave), p = p0 + f;
+    const uint32_t z = hidden(0);
+    // n16 16-byte units of zeros
+    auto zeros = [&](void* dst, int n16) {
+      for (int i = lane; i < n16; i += kWave) static_cast<uint4*>(dst)[i] = uint4{z, z, z, z};
+    };
+    // rows of sums and counts: the parent and its children (flat: R parents)
+    auto rows = [&](int code, int n) {
+      if (lane < n) nb[code + lane] = z;
+      if (vb) zeros(vb + (size_t)code * D, n * D / 4);
+    };
+    if constexpr (kFlat) {
+      rows(R * p, min(R, M0 - R * p));
+    } else {
+      rows(p, 1);
+      rows(M0 + p * Ch, Ch);
+    }
+    if (!pk) return;
+    // n slots of octet o from slot q0 on, or (n a multiple of 8) whole octets
+    auto slots = [&](int o, int q0, int n) {
+      if (n % 8 == 0) {
+        zeros(means + (size_t)o * D * 8, n / 8 * Cfg::OCT_BYTES / 16);
+      } else {
+        for (int i = lane; i < D * n; i += kWave)
+          means[((size_t)o * D + i / n) * 8 + q0 + i % n] = T(__uint_as_float(z));
+      }
+      if (lane < n) {
+        float* io = &info[(size_t)(o + lane / 8) * 16 + q0 + lane % 8];
+        io[0] = __uint_as_float(z);
+        io[8] = kNegInf;
+      }
+    };
+    if constexpr (kFlat) {
+      slots(R * p / 8, R * p % 8, R);
+    } else {
+      slots(PL.PO + p * PL.CO, 0, 8 * PL.CO);
+      for (int i = lane; i < D; i += kWave) pmean[f * D + i] = T(__uint_as_float(z));
+      if (lane == 0) L.cell[f] = __uint_as_float(z);
+    }
+  };
+  {
+    unsigned long long empty = __ballot(lane < nfam && L.hist[lane] == 0);
+    if (empty != 0) {  // the same in every wave
+      for (int i = 0; empty != 0; ++i, empty &= empty - 1)
+        if (i % W == wave) write_empty(__builtin_ctzll(empty));
+      __syncthreads();
+    }
   }
 
   // ---- parent octets (flat: written above, but for the padding) ------------
