@@ -1002,12 +1002,33 @@ hipError_t launch_aggregate_cfg(int BH, int N, int M0, int Ch, const void* V,
 template <typename T, int D>
 constexpr int kSmallKeys = Elem<T>::kBf16 && D == 64 ? 16384 : 1024;
 
+// Beyond that limit, up to 2048 keys, SMALL too where one workgroup per CU takes more
+// than one round (the chain of phases once per round): aggregation with sums,
+// SMALL / one per CU: 300 heads x 64 families, N = 2000, fp32, d = 64 0.89, d = 128
+// 0.95; 214 x 256, N = 1040, Ch = 8, fp32 0.90 and 0.92, bf16, d = 128 0.97 (the fused
+// pass 0.88); 96 x 512, N = 1500 0.92 to 1.02; but 96 x 256, N = 4096, skewed keys up
+// to 1.19. And not for an fp32 flat codebook at d = 128 of fewer families of 16
+// parents than CUs and more than 512 keys, where one skewed family is 4 waves' products: 26 x 64
+// parents, N = 872, skewed 1.21, even 1.06; 48 x 64, N = 800 1.19, 1.11; 64 x 32, N =
+// 1000 1.20, 0.88; against 96 x 512, N = 700 0.99, 0.85.
+template <typename T, int D, int MODE>
+constexpr bool small_workgroups(long long BH, int N, int M0, long long cus) {
+  constexpr bool kFlat = MODE == kAggFlat || MODE == kAggFlatFew;
+  const int n_fam = kFlat ? flat_families(M0, 4) : M0;
+  if (kFlat && !Elem<T>::kBf16 && D == 128 && N > 512 && BH * n_fam <= cus) return false;
+  if (N < kSmallKeys<T, D>) return true;
+  return N < 2048 && BH * ((n_fam + kMaxFamilies - 1) / kMaxFamilies) > cus;
+}
+
 template <typename T, int D, int NT, int MODE>
 hipError_t launch_aggregate_nt(int BH, int N, int M0, int Ch, const void* V,
                                const int32_t* code_idx, float* Vbar, int32_t* counts,
                                void* packed, const FusedArgs& fa, hipStream_t stream) {
   if constexpr (NT == 1) {
-    if (N < kSmallKeys<T, D>)
+    DeviceInfo dev;
+    const hipError_t e = device_info(&dev);
+    if (e != hipSuccess) return e;
+    if (small_workgroups<T, D, MODE>(BH, N, M0, dev.cus > 1 ? dev.cus : 1))
       return launch_aggregate_cfg<T, D, NT, MODE, true>(BH, N, M0, Ch, V, code_idx, Vbar, counts,
                                                         packed, fa, stream);
   }

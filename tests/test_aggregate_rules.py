@@ -33,6 +33,24 @@ static_assert(flat_shift(1, 512, 512, 256) == 4);  // few keys: 16 parents
 // heads of few keys share a compute unit with others, whatever the type
 static_assert(kSmallKeys<bf16, 64> > 4096 && kSmallKeys<bf16, 128> > 512 &&
               kSmallKeys<float, 64> > 512 && kSmallKeys<float, 128> > 512);
+constexpr int C = 256;  // compute units
+static_assert(small_workgroups<bf16, 64, kAggCodes>(48, 4096, 64, C) &&
+              small_workgroups<float, 128, kAggCodes>(1, 700, 64, C) &&
+              small_workgroups<bf16, 128, kAggFused>(1, 700, 64, C) &&
+              small_workgroups<float, 128, kAggFlat>(96, 700, 512, C));
+// up to 2048 keys also others that would take more than one round
+static_assert(small_workgroups<float, 64, kAggCodes>(300, 2000, 64, C) &&
+              small_workgroups<bf16, 128, kAggFused>(214, 1040, 256, C) &&
+              !small_workgroups<bf16, 128, kAggFused>(64, 1040, 256, C) &&
+              !small_workgroups<float, 64, kAggCodes>(96, 4096, 256, C) &&
+              !small_workgroups<float, 64, kAggFlat>(214, 1040, 256, C) &&
+              small_workgroups<float, 128, kAggFlat>(304, 1504, 12, C));
+// few families of fp32 products at d = 128
+static_assert(!small_workgroups<float, 128, kAggFlat>(26, 872, 64, C) &&
+              !small_workgroups<float, 128, kAggFlat>(88, 876, 2, C) &&
+              small_workgroups<float, 128, kAggFlat>(71, 301, 5, C) &&
+              small_workgroups<float, 64, kAggFlat>(26, 872, 64, C) &&
+              small_workgroups<bf16, 128, kAggFlat>(26, 872, 64, C));
 // heads of many keys do not
 static_assert(kSmallKeys<bf16, 64> <= 16384 && kSmallKeys<bf16, 128> <= 4096 &&
               kSmallKeys<float, 64> <= 4096 && kSmallKeys<float, 128> <= 4096);

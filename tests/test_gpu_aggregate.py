@@ -175,10 +175,11 @@ def test_crowded_small_workgroups(Ch, keys, fused):
                                         (torch.float32, 64, 8), (torch.float32, 128, 0),
                                         (torch.float32, 128, 8)])
 @pytest.mark.parametrize("N,M0,heads", [(1, 3, 5), (130, 16, 600), (1023, 100, 300),
-                                        (1023, 512, 3)])
+                                        (1023, 512, 3), (2047, 70, 270), (2048, 70, 270)])
 def test_short_heads(dtype, d, Ch, N, M0, heads):
-    """Heads of fewer than 1024 keys: the small workgroups, two per compute
-    unit, of the other types and widths; codes and (Ch >= 1) the fused pass."""
+    """Heads of fewer than 1024 keys (2048 where they are many): the small
+    workgroups, two per compute unit, of the other types and widths; codes and (Ch
+    >= 1) the fused pass."""
     from paper_2607_12789_amd import avq
     g = torch.Generator(device="cuda").manual_seed(19)
 
