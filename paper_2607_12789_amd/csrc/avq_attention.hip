@@ -180,12 +180,12 @@ void attention_kernel(AttnArgs args) {
   const int groups = (args.n_tiles + TPW - 1) / TPW;
   const int bh = tile / groups, t0 = tile % groups * TPW;
   const int h = bh % args.H;
-  const int sub = wave / Cfg::WPT;  // the wave's tile in the workgroup
+  const int sub = TPW == 1 ? 0 : wave / Cfg::WPT;  // the wave's tile in the workgroup
   const int t = t0 + sub;
   const int q_begin = t * args.block_q;
   const int q_end = min(q_begin + args.block_q, N);
-  const int row0 = q_begin + wave % Cfg::WPT * Cfg::RPW;
-  const bool has_rows = t < args.n_tiles && row0 < q_end;  // wave-uniform
+  const int row0 = q_begin + (TPW == 1 ? wave : wave % Cfg::WPT) * Cfg::RPW;
+  const bool has_rows = (TPW == 1 || t < args.n_tiles) && row0 < q_end;  // wave-uniform
   // waves of tile i with rows
   auto active = [&](int i) {
     const int rows = min(args.block_q, N - (t0 + i) * args.block_q);
