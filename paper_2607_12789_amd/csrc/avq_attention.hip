@@ -108,7 +108,7 @@ struct AttnCfg {
   // faster than two (16 x 8192 in blocks of 128: 329 against 366 us, and 355
   // with two chunk buffers)
   static constexpr int kWavesPerEu =
-      !kB && RPW == 16 ? (D == 64 || MAXW >= 8 ? 4 : 2) : (kB && D == 64) ? 3 : 2;
+      !kB ? (D == 64 || MAXW >= 8 ? 4 : 2) : D == 64 ? 3 : 2;
   static_assert(COPIES % MAXW == 0 || COPIES < MAXW, "copies split evenly over the waves");
   static_assert(OCPY >= 1 && (OCPY & (OCPY - 1)) == 0, "whole wave copies per octet");
 };
@@ -1188,13 +1188,15 @@ hipError_t launch_attention_cfg(const AttnArgs& a, int BH, hipStream_t stream) {
   const long long grid = (long long)BH * ((a.n_tiles + TPW - 1) / TPW);
   if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;
   using Cfg = AttnCfg<T, D, MAXW, TPW, RPW>;
-  // 8 .. 15 and 48 .. 55 one tile (MAXW 4, 8 of RPW 32), 180 .. and 220 .. two
-  // (MAXW 4, 2); fp32 waves of 16 queries 196 .. and 236 ..
+  // LDS-limit slots of their own: bf16 (waves of 32 queries) one tile 8 .. 11 and 48 ..
+  // 51 (tiled), two 180 .. 183 and 220 .. 223; fp32 (of 16) 196 .. 202 and 236 .. 242
+  static_assert(RPW == (Elem<T>::kBf16 ? 32 : 16), "the waves that are launched");
   constexpr int slot =
-      RPW == 16 ? (TILED ? 236 : 196) + (D == 128 ? 4 : 0) +
-                      (MAXW == 16 ? 3 : MAXW == 8 ? 1 : 0) + (TPW == 2 ? 2 : 0)
-                : (TILED ? 48 : 8) + (Elem<T>::kBf16 ? 0 : 4) + (D == 128 ? 2 : 0) +
-                      (MAXW == 8 ? 1 : 0) + (TPW == 2 ? (MAXW == 4 ? 180 : 188) - 8 : 0);
+      Elem<T>::kBf16
+          ? (TILED ? 40 : 0) + (TPW == 2 ? 180 + (MAXW == 4 ? 0 : 1) : 8 + (MAXW == 8 ? 1 : 0)) +
+                (D == 128 ? 2 : 0)
+          : (TILED ? 236 : 196) + (D == 128 ? 4 : 0) + (MAXW == 16 ? 3 : MAXW == 8 ? 1 : 0) +
+                (TPW == 2 ? 2 : 0);
   hipError_t e = ensure_dynamic_lds((const void*)attention_kernel<T, D, MAXW, TPW, RPW, TILED>,
                                     (int)Cfg::LDS_BYTES, slot);
   if (e != hipSuccess) return e;
