@@ -2,15 +2,15 @@
 // convention that a parent row covers its whole cell and a child row the keys
 // that moved to it; and the same pass with the child compare of Alg. 1 in it.
 //
-// A family is a parent and its Ch children (Ch = 0, a flat codebook: 16, 8 or 4
-// consecutive parents, or fewer, see launch_aggregate_cfg). One workgroup owns one (batch, head) and a range of F
-// families and is the only writer of their rows, so there are no float
-// atomics and no partial results in HBM. The workgroup
+// A family is a parent and its Ch children (Ch = 0, a flat codebook: 16, 8, 4,
+// 2 or 1 consecutive parents, see flat_shift). One workgroup owns one (batch,
+// head) and a range of F families and is the only writer of their rows, so
+// there are no float atomics and no partial results in HBM. The workgroup
 //   1. scans the head's codes once: every wave compacts the keys of the range
 //      into a private list in LDS, then counts them per family (integer LDS
 //      atomics on full waves);
-//   2. gives every family whole groups of 32 slots in a key list and scatters
-//      the keys into their family's slots;
+//   2. gives every family with keys whole groups of 32 slots in a key list and
+//      scatters the keys into their family's slots;
 //   3. deals the groups to its waves in equal contiguous runs. For a group
 //      of 32 keys of one family a wave reads the 32 value rows (FUSED: and
 //      the 32 key rows, whose child compare, avq_child.hpp, tells each key's
@@ -33,14 +33,15 @@
 // to the next.
 //
 // What bounds it: at large sizes HBM (each value and key row is read once),
-// at small ones the chain of phases of one workgroup. Before, keys were
-// bucketed a second time by row and each half wave summed one family's rows
-// in turn with vector adds, after a scan with three barriers per 8192 codes.
-// The precompute (parent assignment + fused pass), bf16, us, before -> now:
-// B = 2, H = 16, N = 16384, d = 128, M0 = 256, Ch = 8: 104 -> 96 (the pass
-// itself reads K and V at about 4.7 TB/s once it streams); B = 1, H = 16,
-// N = 65536, M0 = 512: 282 -> 261; B = 8, H = 12, N = 4096, d = 64, M0 = 256:
-// 89 -> 58; B = 4, H = 12, N = 1024, d = 64, M0 = 64: 35 -> 17.
+// at small ones the chain of phases of one workgroup; with few keys per family
+// (about 16 and less) a wave's stores: the wait for the next group's rows is
+// one for the family's stores as well. The precompute (parent assignment +
+// fused pass), bf16, us, one row of a family after the other by vector adds ->
+// by these products: B = 2, H = 16, N = 16384, d = 128, M0 = 256, Ch = 8: 104 ->
+// 96 (the pass itself reads K and V at about 4.7 TB/s once it streams); B = 1,
+// H = 16, N = 65536, M0 = 512: 282 -> 261; B = 8, H = 12, N = 4096, d = 64, M0 =
+// 256: 89 -> 58; B = 4, H = 12, N = 1024, d = 64, M0 = 64: 35 -> 17. Aggregation
+// with sums, fp32, d = 128, 96 x 512 families, N = 1500, Ch = 8: 128 -> 152.
 //
 // Packed aggregates (avq_packed.hpp): the mean value (sum / count) of every
 // code rounded to the input type, in octets of 8 codes laid out as the
@@ -938,9 +939,11 @@ void aggregate_kernel(
 // families per workgroup cost scanning (every workgroup scans all codes of
 // its head) and a second round, more leave CUs idle. Precompute in us: 48
 // heads of 64 families (N = 1024, d = 64, 1024 slots): 2 families 21.1, 4
-// 17.3 (chosen), 8 18.0, 16 21.9; 96 heads of 256 (N = 4096): 24 67.3, 32
-// 57.7 (chosen), 64 76.2; 32 heads of 256 (N = 16384, d = 128, 256 slots): 16
-// 104, 32 96 (chosen), 64 123.
+// 17.3, 8 18.0, 16 21.9 (4 taken); 32 heads of 256 (N = 16384, d = 128, 256 slots):
+// 16 104, 32 96, 64 123 (32 taken); 96 heads of 256 (N = 4096, 1024 slots), keys even
+// / on few codes: 26 60.4 / 90.9, 32 57.7 / 113.1 (26 taken). Whole octets of
+// parents (a multiple of 8) save the parts of an octet at the end, but over 22
+// shapes they were 0.95 to 1.24 of the time, mostly more.
 inline int families_per_workgroup(long long BH, int n_fam, long long slots) {
   const long long least = (n_fam + kMaxFamilies - 1) / kMaxFamilies;  // ranges per head
   const long long rounds = std::max(1LL, (least * BH + slots - 1) / slots);
@@ -1002,15 +1005,15 @@ hipError_t launch_aggregate_cfg(int BH, int N, int M0, int Ch, const void* V,
 template <typename T, int D>
 constexpr int kSmallKeys = Elem<T>::kBf16 && D == 64 ? 16384 : 1024;
 
-// Beyond that limit, up to 2048 keys, SMALL too where one workgroup per CU takes more
-// than one round (the chain of phases once per round): aggregation with sums,
+// Beyond that limit, up to 2048 keys, SMALL too where one workgroup per CU takes
+// more than one round (the chain of phases once per round): aggregation with sums,
 // SMALL / one per CU: 300 heads x 64 families, N = 2000, fp32, d = 64 0.89, d = 128
 // 0.95; 214 x 256, N = 1040, Ch = 8, fp32 0.90 and 0.92, bf16, d = 128 0.97 (the fused
 // pass 0.88); 96 x 512, N = 1500 0.92 to 1.02; but 96 x 256, N = 4096, skewed keys up
 // to 1.19. And not for an fp32 flat codebook at d = 128 of fewer families of 16
-// parents than CUs and more than 512 keys, where one skewed family is 4 waves' products: 26 x 64
-// parents, N = 872, skewed 1.21, even 1.06; 48 x 64, N = 800 1.19, 1.11; 64 x 32, N =
-// 1000 1.20, 0.88; against 96 x 512, N = 700 0.99, 0.85.
+// parents than CUs and more than 512 keys, where one skewed family is 4 waves'
+// products: 26 x 64 parents, N = 872, skewed 1.21, even 1.06; 48 x 64, N = 800
+// 1.19, 1.11; 64 x 32, N = 1000 1.20, 0.88; against 96 x 512, N = 700 0.99, 0.85.
 template <typename T, int D, int MODE>
 constexpr bool small_workgroups(long long BH, int N, int M0, long long cus) {
   constexpr bool kFlat = MODE == kAggFlat || MODE == kAggFlatFew;

@@ -88,17 +88,17 @@ EDGE = {
     "flat_fp32_d128": small(Ch=0, P=0, dtype="f32", d=128, block_q=64),
     "flat_m0_300_split": small(Ch=0, P=0, M0=300, B=1, H=1, N=2000),
     "flat_m0_512_d128": small(Ch=0, P=0, M0=512, d=128, N=1536, B=1, H=2, block_q=256),
-    # few workgroups and at least 256 keys per parent: two or four half waves
-    # share a family in the aggregation (on a 256-CU device: two for 64 heads
-    # of 32 parents, four for fewer)
+    # few families and at least 256 keys per parent: a family's groups of keys
+    # are dealt to several waves, whose parts are added in LDS (in the flat
+    # case one parent per family)
     "agg_split2": small(M0=32, Ch=4, P=4, N=8192, B=8, H=8, block_q=256),
     "agg_split4": small(M0=8, Ch=8, P=3, N=4200, B=1, H=2, block_q=256),
     "agg_split4_ragged_fp32_d128": small(dtype="f32", M0=20, Ch=2, P=4, N=11000, d=128, B=1,
                                          H=1, block_q=256),
     "agg_split4_flat": small(Ch=0, P=0, M0=16, N=9000, B=1, H=2, block_q=256),
     "agg_split4_ch16": small(M0=10, Ch=16, P=3, N=2600, B=1, H=2),
-    # every key of a head in one workgroup's range, more than its key queue
-    # holds: the queue is bucketed and summed in the middle of the scan
+    # the same with thousands of keys per parent, most of what one workgroup
+    # lists (lists that do not hold their keys: test_gpu_aggregate.py)
     "agg_queue_overflow": small(M0=8, Ch=8, P=3, N=20000, B=1, H=2, block_q=256),
     "agg_queue_overflow_d128": small(M0=8, Ch=8, P=3, N=20000, B=1, H=2, block_q=256,
                                      d=128),
