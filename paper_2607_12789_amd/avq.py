@@ -9,6 +9,7 @@ built, every call raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from pathlib import Path
 from typing import Optional
@@ -140,6 +141,11 @@ def packed_bytes(dtype: torch.dtype, M0: int, Ch: int, d: int) -> int:
     return n
 
 
+# The same for sizes that are a tensor's own (plain ints, so equal keys are
+# equal sizes): 0.1 us where the library call takes 0.9.
+_packed_bytes_of = functools.lru_cache(maxsize=256)(packed_bytes)
+
+
 def aggregate(V, code_idx, M0: int, Ch: int, packed=None, counts=None, Vbar=None,
               sums: bool = False, stream=None):
     """Per-codeword counts, packed aggregates and optionally fp32 sums (``avq_aggregate``).
@@ -186,7 +192,7 @@ def assign_aggregate(K, V, Cp, Cc, parent_idx=None, code_idx=None, packed=None, 
         parent_idx = torch.empty((B, H, N), dtype=torch.int32, device=dev)
     if code_idx is None:
         code_idx = torch.empty((B, H, N), dtype=torch.int32, device=dev)
-    E = packed_bytes(K.dtype, M0, Ch, d)
+    E = _packed_bytes_of(K.dtype, M0, Ch, d)
     if packed is None:
         packed = torch.empty((B, H, E), dtype=torch.uint8, device=dev)
     if counts is None:
@@ -242,7 +248,7 @@ def attention_fwd(Q, Cp, Cc, packed, P: int, block_q: int, Y=None, topp_idx=None
     _dev(Q, "Q")
     _dev(Cp, "Cp", Q.dtype, (H, M0, d))
     _dev(Cc, "Cc", Q.dtype, (H, M0, Ch, d))
-    _dev(packed, "packed", torch.uint8, (B, H, packed_bytes(Q.dtype, M0, Ch, d)))
+    _dev(packed, "packed", torch.uint8, (B, H, _packed_bytes_of(Q.dtype, M0, Ch, d)))
     if Y is None:
         Y = torch.empty_like(Q)
     _dev(Y, "Y", Q.dtype, Q.shape)

@@ -126,6 +126,20 @@ def test_packed_bytes_takes_integer_objects(L):
     assert avq.packed_bytes(torch.bfloat16, m0, 8, 64) == want[1]
 
 
+def test_packed_bytes_of_tensor_sizes(L):
+    """What the entry points keep per tensor sizes: the same sizes, and the
+    same error at every call."""
+    for dtype in (torch.float32, torch.bfloat16):
+        for M0, Ch, d in ((1, 0, 64), (37, 16, 64), (512, 8, 128)):
+            for _ in range(2):
+                assert avq._packed_bytes_of(dtype, M0, Ch, d) == avq.packed_bytes(dtype, M0, Ch, d)
+    for _ in range(2):
+        with pytest.raises(ValueError, match="invalid sizes"):
+            avq._packed_bytes_of(torch.bfloat16, 513, 8, 64)
+        with pytest.raises(ValueError, match="unsupported dtype"):
+            avq._packed_bytes_of(torch.float16, 64, 8, 64)
+
+
 def test_misaligned_pointers_are_rejected(L):
     odd = ctypes.c_void_p(24)
     assert assign(L, ptrs=(odd,) + (FAKE,) * 4) == INVALID
